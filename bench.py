@@ -123,7 +123,7 @@ def copy_calibration(mib):
 
 # the translation unit of the FFT passes (the kernels whose counters are
 # recorded): their source file and every header it includes
-FFT_PASS_SOURCES = ("gps_fft_fast.hip", "gps_fft_reg.h", "gps_iter.h", "gps_launch.h",
+FFT_PASS_SOURCES = ("gps_fft_fast.hip", "gps_fft_two.h", "gps_fft_reg.h", "gps_iter.h", "gps_launch.h",
                     "gps_device.h", "gps_internal.h")
 
 

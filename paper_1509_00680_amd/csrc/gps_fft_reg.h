@@ -9,21 +9,44 @@
 namespace gps {
 
 // ---- constexpr cos/sin(2 pi m / n) ------------------------------------------
-__host__ __device__ constexpr double ce_sin_series(double x) {
-  double term = x, sum = x;
-  for (int i = 1; i < 14; ++i) {
-    term *= -x * x / ((2.0 * i) * (2.0 * i + 1.0));
-    sum += term;
-  }
-  return sum;
+// Evaluated in double-double arithmetic (Dekker's split product, Knuth's sum)
+// and rounded once: the plain binary64 series is off by up to 2.3 units in the
+// last place at N = 25.
+struct DD {
+  double hi, lo;
+};
+constexpr DD dd_sum(double a, double b) {            // a + b exactly
+  const double s = a + b, t = s - a;
+  return DD{s, (a - (s - t)) + (b - t)};
 }
-__host__ __device__ constexpr double ce_cos_series(double x) {
-  double term = 1.0, sum = 1.0;
+constexpr DD dd_prod(double a, double b) {           // a b exactly
+  const double p = a * b;
+  const double ca = 134217729.0 * a, ah = ca - (ca - a), al = a - ah;
+  const double cb = 134217729.0 * b, bh = cb - (cb - b), bl = b - bh;
+  return DD{p, ((ah * bh - p) + ah * bl + al * bh) + al * bl};
+}
+constexpr DD dd_add(DD a, DD b) {
+  const DD s = dd_sum(a.hi, b.hi);
+  return dd_sum(s.hi, s.lo + (a.lo + b.lo));
+}
+constexpr DD dd_mul(DD a, DD b) {
+  const DD p = dd_prod(a.hi, b.hi);
+  return dd_sum(p.hi, p.lo + (a.hi * b.lo + a.lo * b.hi));
+}
+constexpr DD dd_div(DD a, double b) {
+  const double q = a.hi / b;
+  const DD p = dd_prod(q, b);
+  return dd_sum(q, (((a.hi - p.hi) - p.lo) + a.lo) / b);
+}
+// sum_i (-1)^i x^(2i+k) / (2i+k)!: sin (k = 1) and cos (k = 0) of 0 <= x <= pi/4
+__host__ __device__ constexpr double ce_series(DD x, int k) {
+  const DD x2 = dd_mul(x, x);
+  DD term = k ? x : DD{1.0, 0.0}, sum = term;
   for (int i = 1; i < 14; ++i) {
-    term *= -x * x / ((2.0 * i - 1.0) * (2.0 * i));
-    sum += term;
+    term = dd_div(dd_mul(term, x2), -(2.0 * i + k - 1.0) * (2.0 * i + k));
+    sum = dd_add(sum, term);
   }
-  return sum;
+  return sum.hi;
 }
 // angle 2 pi m/n reduced to the first octant by exact integer symmetries
 __host__ __device__ constexpr void ce_root(long long m, long long n, double* c, double* s) {
@@ -35,8 +58,9 @@ __host__ __device__ constexpr void ce_root(long long m, long long n, double* c, 
   // theta = 2 pi m/n = q pi/2 + phi, phi = (pi/2) r4/n
   bool swap = 2 * r4 > n;               // phi > pi/4: use pi/2 - phi
   long long num = swap ? (n - r4) : r4;
-  double phi = 1.5707963267948966192313216916398 * (double)num / (double)n;
-  double sp = ce_sin_series(phi), cp = ce_cos_series(phi);
+  const DD half_pi{1.5707963267948966, 6.123233995736766e-17};
+  const DD phi = dd_div(dd_mul(half_pi, DD{(double)num, 0.0}), (double)n);
+  double sp = ce_series(phi, 1), cp = ce_series(phi, 0);
   if (swap) { double t = sp; sp = cp; cp = t; }
   double cc = cp, ss = sp;
   if (q == 1) { cc = -sp; ss = cp; }
@@ -46,12 +70,21 @@ __host__ __device__ constexpr void ce_root(long long m, long long n, double* c, 
   *s = ss;
 }
 
-// w_N^e = exp(-2 pi i e/N) (forward) or its conjugate (inverse).  Called with
-// indices that are constant after unrolling, so the series folds to literals.
+// cos and sin(2 pi m / N), m < N, evaluated by the front end.
+template <int N> struct RootTable {
+  double c[N], s[N];
+  constexpr RootTable() : c{}, s{} {
+    for (int m = 0; m < N; ++m) ce_root(m, N, &c[m], &s[m]);
+  }
+};
+template <int N> struct Roots2Pi { static constexpr RootTable<N> t{}; };
+
+// w_N^e = exp(-2 pi i e/N) (forward) or its conjugate (inverse), 0 <= e < N.
+// Called with indices that are constant after unrolling, so the table reads
+// fold to literals.
 template <typename T, int N, bool INV>
 __device__ __forceinline__ cplx<T> croot(int e) {
-  double c = 0.0, s = 0.0;
-  ce_root(e, N, &c, &s);
+  const double c = Roots2Pi<N>::t.c[e], s = Roots2Pi<N>::t.s[e];
   return cmk(T(c), T(INV ? s : -s));
 }
 
@@ -79,6 +112,13 @@ template <> struct OddRoots<5> {
   static constexpr double s[3] = {0.0, 0.95105651629515357212, 0.58778525229247312917};
 };
 
+template <> struct OddRoots<7> {
+  static constexpr double c[4] = {1.0, 0.62348980185873353053, -0.22252093395631440429,
+                                  -0.90096886790241912624};
+  static constexpr double s[4] = {0.0, 0.78183148246802980871, 0.97492791218182360702,
+                                  0.43388373911755812048};
+};
+
 template <typename T, bool INV, int R>
 __device__ __forceinline__ void rdft(cplx<T>* x) {
   if constexpr (R == 2) {
@@ -94,7 +134,7 @@ __device__ __forceinline__ void rdft(cplx<T>* x) {
     x[1] = cadd(a1, ja3);
     x[3] = csub(a1, ja3);
   } else {
-    static_assert(R == 3 || R == 5, "radix");
+    static_assert(R == 3 || R == 5 || R == 7, "radix");
     constexpr int H = (R - 1) / 2;
     cplx<T> a[H + 1], b[H + 1];
 #pragma unroll
@@ -223,14 +263,21 @@ GPS_CODELET(2, 2)
 GPS_CODELET(3, 3)
 GPS_CODELET(4, 4)
 GPS_CODELET(5, 5)
+GPS_CODELET(7, 7)
 GPS_CODELET(8, 4, 2)
+GPS_CODELET(9, 3, 3)
 GPS_CODELET(16, 4, 4)
-GPS_CODELET(32, 4, 4, 2)
+GPS_CODELET(25, 5, 5)
 GPS_PFA_CODELET(6, 2, 3)
 GPS_PFA_CODELET(10, 2, 5)
 GPS_PFA_CODELET(12, 4, 3)
+GPS_PFA_CODELET(14, 2, 7)
+GPS_PFA_CODELET(15, 3, 5)
+GPS_PFA_CODELET(18, 2, 9)
 GPS_PFA_CODELET(20, 4, 5)
+GPS_PFA_CODELET(21, 3, 7)
 GPS_PFA_CODELET(24, 8, 3)
+GPS_PFA_CODELET(28, 4, 7)
 #undef GPS_CODELET
 #undef GPS_PFA_CODELET
 

@@ -108,11 +108,25 @@ template <typename T> void launch_strided(int mode, const SParams<T>& p, hipStre
 // the number of pencils plus 64).
 template <typename T> int strided_parts(const SParams<T>& p);
 
-// Two-level passes for the common lengths (32 ... 384); false if L has none.
+// Two-level passes (gps_fft_two.h).  One entry per length that has them; a
+// length without an entry takes the generic passes.  The entries of
+// gps_fft_fast.hip and gps_fft_lengths.hip add themselves when the library is
+// loaded.
+struct LengthPasses {
+  int L, L1, L2;            // L = L1 L2
+  int P;                    // row pairs per work-group of the x passes
+  void (*strided32)(int mode, const SParams<float>& p, hipStream_t s);
+  void (*strided64)(int mode, const SParams<double>& p, hipStream_t s);
+  bool (*xfwd32)(int mode, const XParams<float>& p, hipStream_t s);
+  bool (*xfwd64)(int mode, const XParams<double>& p, hipStream_t s);
+  bool (*xinv32)(int mode, const XParams<float>& p, hipStream_t s);
+  bool (*xinv64)(int mode, const XParams<double>& p, hipStream_t s);
+};
+constexpr int kMaxFastLen = 448;     // longest length with two-level passes
+bool add_length_passes(const LengthPasses& e);
 bool fast_length(int L);
 int fast_xpass_groups(int L, int nrows);
 int fast_xpass_parts(int L, int nrows);
-template <typename T> int fast_strided_groups(int npencils, int B);
 template <typename T> int fast_strided_parts(const SParams<T>& p);   // z pass (solve mode)
 template <typename T> bool fast_strided(int mode, const SParams<T>& p, hipStream_t s);
 template <typename T> bool fast_xfwd(int mode, const XParams<T>& p, hipStream_t s);
