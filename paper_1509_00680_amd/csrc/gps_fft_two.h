@@ -43,6 +43,12 @@ constexpr int larger(int a, int b) { return a > b ? a : b; }
 template <typename T>
 __device__ __forceinline__ cplx<T> cconj(cplx<T> a) { return cmk(a.x, -a.y); }
 
+// Load by components: a complex FP64 value copied as a whole into an array that
+// lives across a branch is given a stack slot (a wait for the load, a store to
+// scratch memory and a second load), its two parts are not.
+template <typename T>
+__device__ __forceinline__ cplx<T> load_parts(const cplx<T>* p) { return cmk(p->x, p->y); }
+
 // Store of a value that the next kernel reads on other XCDs (the transposes
 // around the z pass): non-temporal, so the line does not stay dirty in this
 // XCD's L2 until the end-of-kernel write-back.  Large outputs of the y-forward
@@ -95,7 +101,7 @@ void k_fstrided(SParams<T> p) {
   cplx<T> twv[(L + NT - 1) / NT];
 #pragma unroll
   for (int i = 0; i < (L + NT - 1) / NT; ++i)
-    twv[i] = p.tw[min(tid + i * NT, L - 1)];    // clamped: no branch around the load
+    twv[i] = load_parts(&p.tw[min(tid + i * NT, L - 1)]);   // clamped: no branch around the load
   const int b = tid & (B - 1);
   const int q = tid / B;
   // (xcd_tile maps work-group 0 to tile 0, so the shift keeps every XCD's
@@ -208,7 +214,7 @@ void k_fstrided(SParams<T> p) {
   const int flag = st ? stop_flag_issue(st) : 0;
 #pragma unroll
   for (int i = 0; i < (L + NT - 1) / NT; ++i)
-    if (tid + i * NT < L) twl[tid + i * NT] = twv[i];
+    if (tid + i * NT < L) twl[tid + i * NT] = cmk(twv[i].x, twv[i].y);
   if (stop_flag_set(flag)) return;
   __syncthreads();
   const cplx<T>* tw = twl;
@@ -403,7 +409,7 @@ void k_fxfwd(XParams<T> p) {
   cplx<T> twv[ETW];
 #pragma unroll
   for (int i = 0; i < ETW; ++i)
-    twv[i] = p.tw[min(tid + i * NT, L - 1)];    // clamped: no branch around the load
+    twv[i] = load_parts(&p.tw[min(tid + i * NT, L - 1)]);   // clamped: no branch around the load
   // the head's own loads (state words, (p, Ap) partials) go first, then the
   // operands of the r update and of the transform (r, 1/sqrt(eps), Ap), then
   // those of the phi (and s) update (p, phi), which are used only after the
@@ -490,7 +496,7 @@ void k_fxfwd(XParams<T> p) {
   }
 #pragma unroll
   for (int i = 0; i < ETW; ++i)
-    if (tid + i * NT < L) twl[tid + i * NT] = twv[i];
+    if (tid + i * NT < L) twl[tid + i * NT] = cmk(twv[i].x, twv[i].y);
   __syncthreads();
   const int pp = tid % P;
   const int q = tid / P;
@@ -603,7 +609,7 @@ void k_fxinv(XParams<T> p) {
   cplx<T> twv[ETW];
 #pragma unroll
   for (int i = 0; i < ETW; ++i)
-    twv[i] = p.tw[min(tid + i * NT, L - 1)];    // clamped: no branch around the load
+    twv[i] = load_parts(&p.tw[min(tid + i * NT, L - 1)]);   // clamped: no branch around the load
   unsigned roff[2 * P];
   bool rok[2 * P];
   tile_row_offsets<2 * P>(p, row0, Kx, roff, rok);
@@ -667,7 +673,7 @@ void k_fxinv(XParams<T> p) {
   }
 #pragma unroll
   for (int i = 0; i < ETW; ++i)
-    if (tid + i * NT < L) twl[tid + i * NT] = twv[i];
+    if (tid + i * NT < L) twl[tid + i * NT] = cmk(twv[i].x, twv[i].y);
   __syncthreads();
   const int pp = tid % P;
   const int q = tid / P;
