@@ -178,6 +178,7 @@ struct gps_plan {
   double* lap64t = nullptr;     // spectral Laplacian table (periodic)
   double* pol_lne = nullptr;    // ln eps scratch of gps_polarization_charge (n doubles)
   size_t pol_bytes = 0;
+  int* bad_atoms = nullptr;     // pinned: flag of gps_rigid_cavity's atom check
   // Algorithm SC / PSD (gps_solve_sc): FP64 fields, partials, device state and
   // captured iteration graphs of 8, 4, 2 and 1 steps
   struct ScRes {
@@ -1461,6 +1462,8 @@ static void plan_release(gps_plan* pl) {
   dfree(pl->lap32t);
   dfree(pl->pol_lne);
   pl->pol_bytes = 0;
+  if (pl->bad_atoms) (void)hipHostFree(pl->bad_atoms);
+  pl->bad_atoms = nullptr;
   free_sc(pl);
 }
 
@@ -1677,20 +1680,17 @@ gps_status gps_rigid_cavity(gps_plan* pl, int natoms, const double* atoms, doubl
       !(eps0 >= 1.0) || !std::isfinite(eps0))
     return GPS_E_INVALID;
   try {
-    // the atom table is checked on the host (finite centres, radii > 0)
-    std::vector<double> h((size_t)natoms * 4);
-    ck(hipMemcpyAsync(h.data(), atoms, h.size() * sizeof(double), hipMemcpyDeviceToHost,
-                      pl->stream()));
-    ck(hipStreamSynchronize(pl->stream()));
-    for (int a = 0; a < natoms; ++a) {
-      const double* at = &h[(size_t)a * 4];
-      if (!std::isfinite(at[0]) || !std::isfinite(at[1]) || !std::isfinite(at[2]) ||
-          !(at[3] > 0.0) || !std::isfinite(at[3]))
-        return GPS_E_INVALID;
+    if (!pl->bad_atoms &&
+        hipHostMalloc(reinterpret_cast<void**>(&pl->bad_atoms), sizeof(int)) != hipSuccess) {
+      (void)hipGetLastError();
+      pl->bad_atoms = nullptr;
+      throw DevError{hipErrorOutOfMemory};
     }
-    launch_rigid_cavity(pl->g, atoms, natoms, delta, eps0, eps, q, pl->stream());
+    *pl->bad_atoms = 0;
+    launch_rigid_cavity(pl->g, atoms, natoms, delta, eps0, eps, q, pl->bad_atoms, pl->stream());
     ck(hipGetLastError());
     ck(hipStreamSynchronize(pl->stream()));
+    if (*static_cast<volatile int*>(pl->bad_atoms)) return GPS_E_INVALID;
   } catch (const DevError& d) {
     pl->info.device_error = (int)d.e;
     return GPS_E_DEVICE;

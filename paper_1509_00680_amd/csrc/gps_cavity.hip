@@ -32,6 +32,18 @@ namespace gps {
 // below 1e-17 / Delta^2, far below the rounding of max|q| ~ (eps0 - 1)/Delta^2.  A work-group covers an 8 x 8 x 4 block of grid
 // points (a wavefront an 8 x 8 patch of one plane), so the lanes of a
 // wavefront are near the same atoms and skip the same ones.
+//
+// Bound by FP64 arithmetic.  A work-group first lists, 256 atoms at a time and
+// in their order, those that some point of its block can see: the distance to
+// the nearest image changes by no more than the point moves, so an atom whose
+// distance from the block's centre exceeds d + kFarT Delta by the half
+// diagonal is far from every point.  The other atoms used to cost every point
+// a square root and about 50 FP64 instructions: 96^3 points, 24 atoms in a ball of
+// 6 bohr: 40.1 -> @@K us.  The results are the same to the bit.
+//
+// The atom table is checked here (finite centres, radii > 0), where every
+// work-group reads all of it anyway, instead of in a copy on the host: on a bad
+// entry no work-group writes, and the first one raises *bad.
 constexpr double kFarT = 6.5;
 constexpr int kCBX = 8, kCBY = 8, kCBZ = kThreads / (kCBX * kCBY);
 
@@ -39,7 +51,9 @@ __global__ __launch_bounds__(kThreads) void k_rigid_cavity(Geom g, int nbx, int 
                                                            const double* __restrict__ atoms,
                                                            int natoms, double delta, double eps0,
                                                            double* __restrict__ eps,
-                                                           double* __restrict__ q) {
+                                                           double* __restrict__ q, int* bad) {
+  __shared__ double near[4 * kThreads];
+  __shared__ int wave_near[kThreads / 64], wave_bad[kThreads / 64];
   const int tid = threadIdx.x;
   const int b = blockIdx.x;
   const int bz = b / (nbx * nby);
@@ -48,34 +62,89 @@ __global__ __launch_bounds__(kThreads) void k_rigid_cavity(Geom g, int nbx, int 
   const int ix = bx * kCBX + tid % kCBX;
   const int iy = by * kCBY + (tid / kCBX) % kCBY;
   const int iz = bz * kCBZ + tid / (kCBX * kCBY);
-  if (ix >= g.nx || iy >= g.ny || iz >= g.nz) return;
   const double x = (ix - 0.5 * (g.nx - 1)) * g.h;
   const double y = (iy - 0.5 * (g.ny - 1)) * g.h;
   const double z = (iz - 0.5 * (g.nz - 1)) * g.h;
   const double lx = g.nx * g.h, ly = g.ny * g.h, lz = g.nz * g.h;
   const double idelta = 1.0 / delta;
   const double cu = 2.0 / (delta * 1.7724538509055160273);   // 2 / (Delta sqrt(pi))
+  // centre of the block and its half diagonal
+  const double cx = (bx * kCBX + 0.5 * (kCBX - 1) - 0.5 * (g.nx - 1)) * g.h;
+  const double cy = (by * kCBY + 0.5 * (kCBY - 1) - 0.5 * (g.ny - 1)) * g.h;
+  const double cz = (bz * kCBZ + 0.5 * (kCBZ - 1) - 0.5 * (g.nz - 1)) * g.h;
+  const double reach = 0.5 * g.h * sqrt(double((kCBX - 1) * (kCBX - 1) +
+                                               (kCBY - 1) * (kCBY - 1) +
+                                               (kCBZ - 1) * (kCBZ - 1)));
   double H = 1.0, gx = 0.0, gy = 0.0, gz = 0.0, w = 0.0;
-  for (int a = 0; a < natoms; ++a) {
-    const double* at = atoms + 4 * a;
-    double dx = x - at[0], dy = y - at[1], dz = z - at[2];
-    if (g.periodic_x) dx -= lx * rint(dx / lx);
-    if (g.periodic_y) dy -= ly * rint(dy / ly);
-    if (g.periodic_z) dz -= lz * rint(dz / lz);
-    const double r = sqrt(dx * dx + dy * dy + dz * dz);
-    const double t = (r - at[3]) * idelta;
-    if (t > kFarT) continue;
-    H *= 0.5 * erfc(-t);
-    const double u = cu / erfcx(-t);
-    w -= 2.0 * t * u * idelta;
-    if (r > 0.0) {
-      const double ur = u / r;
-      gx += ur * dx;
-      gy += ur * dy;
-      gz += ur * dz;
-      w += 2.0 * ur - u * u;
+  for (int a0 = 0; a0 < natoms; a0 += kThreads) {
+    bool is_near = false, is_bad = false;
+    double ax = 0.0, ay = 0.0, az = 0.0, ad = 0.0;
+    if (a0 + tid < natoms) {
+      const double* at = atoms + 4 * (size_t)(a0 + tid);
+      ax = at[0];
+      ay = at[1];
+      az = at[2];
+      ad = at[3];
+      is_bad = !isfinite(ax) || !isfinite(ay) || !isfinite(az) || !(ad > 0.0) || !isfinite(ad);
+      double dx = cx - ax, dy = cy - ay, dz = cz - az;
+      if (g.periodic_x) dx -= lx * rint(dx / lx);
+      if (g.periodic_y) dy -= ly * rint(dy / ly);
+      if (g.periodic_z) dz -= lz * rint(dz / lz);
+      const double r = sqrt(dx * dx + dy * dy + dz * dz);
+      // (a relative margin for the rounding of both sides)
+      is_near = r * (1.0 - 1e-12) - reach <= (ad + kFarT * delta) * (1.0 + 1e-12) +
+                                                 1e-12 * (fabs(ax) + fabs(ay) + fabs(az));
     }
+    const unsigned long long mask = __ballot(is_near);
+    const int lane = tid & 63, wave = tid >> 6;
+    const unsigned long long bad_mask = __ballot(is_bad);
+    if (lane == 0) {
+      wave_near[wave] = __popcll(mask);
+      wave_bad[wave] = bad_mask != 0;
+    }
+    __syncthreads();
+    int pos = 0, count = 0, any_bad = 0;
+#pragma unroll
+    for (int v = 0; v < kThreads / 64; ++v) {
+      if (v < wave) pos += wave_near[v];
+      count += wave_near[v];
+      any_bad |= wave_bad[v];
+    }
+    if (any_bad) {                                 // the same for the whole work-group
+      if (b == 0 && tid == 0) *bad = 1;
+      return;
+    }
+    if (is_near) {
+      double* e = near + 4 * (pos + __popcll(mask & ((1ull << lane) - 1ull)));
+      e[0] = ax;
+      e[1] = ay;
+      e[2] = az;
+      e[3] = ad;
+    }
+    __syncthreads();
+    for (int a = 0; a < count; ++a) {
+      const double* at = near + 4 * a;
+      double dx = x - at[0], dy = y - at[1], dz = z - at[2];
+      if (g.periodic_x) dx -= lx * rint(dx / lx);
+      if (g.periodic_y) dy -= ly * rint(dy / ly);
+      if (g.periodic_z) dz -= lz * rint(dz / lz);
+      const double r = sqrt(dx * dx + dy * dy + dz * dz);
+      const double t = (r - at[3]) * idelta;
+      if (t > kFarT) continue;
+      H *= 0.5 * erfc(-t);
+      const double u = cu / erfcx(-t);
+      w -= 2.0 * t * u * idelta;
+      if (r > 0.0) {
+        const double ur = u / r;
+        gx += ur * dx;
+        gy += ur * dy;
+        gz += ur * dz;
+        w += 2.0 * ur - u * u;
+      }
+    }
+    __syncthreads();                               // the list is read before the next atoms
   }
+  if (ix >= g.nx || iy >= g.ny || iz >= g.nz) return;
   const size_t i = ((size_t)iz * g.ny + iy) * g.nx + ix;
   const double a = eps0 - 1.0;
   const double aH = a * H;
@@ -88,11 +157,11 @@ __global__ __launch_bounds__(kThreads) void k_rigid_cavity(Geom g, int nbx, int 
 }
 
 void launch_rigid_cavity(const Geom& g, const double* atoms, int natoms, double delta,
-                         double eps0, double* eps, double* q, hipStream_t s) {
+                         double eps0, double* eps, double* q, int* bad, hipStream_t s) {
   const int nbx = (g.nx + kCBX - 1) / kCBX, nby = (g.ny + kCBY - 1) / kCBY;
   const int nbz = (g.nz + kCBZ - 1) / kCBZ;
   GPS_LAUNCH(k_rigid_cavity, dim3((unsigned)(nbx * nby * nbz)), dim3(kThreads), 0, s, g, nbx,
-             nby, atoms, natoms, delta, eps0, eps, q);
+             nby, atoms, natoms, delta, eps0, eps, q, bad);
 }
 
 // ---------------------------------------------------------------------------

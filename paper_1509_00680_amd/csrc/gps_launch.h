@@ -195,8 +195,10 @@ template <typename T> void launch_refine(const SlotTable<T>& tab, const Batch& b
                                          hipStream_t s);
 
 // Cavity builder and diagnostics (gps_cavity.hip)
+// *bad (host memory the device can write) is set to 1, and nothing else is
+// written, if an atom's centre is not finite or its radius not positive.
 void launch_rigid_cavity(const Geom& g, const double* atoms, int natoms, double delta,
-                         double eps0, double* eps, double* q, hipStream_t s);
+                         double eps0, double* eps, double* q, int* bad, hipStream_t s);
 void launch_log_field(long long n, const double* eps, double* lne, hipStream_t s);
 // Device address of the no-allocation scratch array (kNoAllocMaxPoints
 // doubles) on `device`, which must be the current device; looked up once per

@@ -1,0 +1,78 @@
+"""The rigid cavity's atom lists (a work-group keeps the atoms its block can see, 256 at a
+time) and its check of the atom table: counts around a list's size, ragged blocks, every
+boundary condition, and bad entries in any part of the table.  Tolerances of the cavity parity
+tests: eps within 1e-13 eps0, q within 1e-10 max|q| of the same formula in numpy over all atoms
+(the oracle's product rule is cubic in the atoms)."""
+import numpy as np
+import pytest
+
+from scipy.special import erfc, erfcx
+from paper_1509_00680_amd import gps
+from gpu_util import dev, host, empty, plan, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+SHAPE, H = (21, 36, 42), 0.6
+DELTA, EPS0 = 0.25, 78.36
+
+
+def _atoms(n, seed):
+    rng = np.random.default_rng(seed)
+    half = 0.5 * H * np.array(SHAPE[::-1])
+    return np.concatenate([rng.uniform(-1.2 * half, 1.2 * half, (n, 3)),   # some outside the box
+                           rng.uniform(0.5, 0.9, (n, 1))], axis=1)
+
+
+def _reference(atoms, bc):
+    """eps = a prod h + 1 and q = (a H/2)(|G|^2 + W) - (a H)^2 |G|^2 / (4 eps), a = eps0 - 1,
+    G and W the sums of the logarithmic derivatives over every atom."""
+    per = {"free": (0, 0, 0), "surface": (0, 1, 1), "periodic": (1, 1, 1), "wire": (1, 0, 0)}[bc]
+    ax = [(np.arange(n) - (n - 1) / 2.0) * H for n in SHAPE]      # z, y, x
+    prod, w, g = np.ones(SHAPE), np.zeros(SHAPE), [np.zeros(SHAPE) for _ in range(3)]
+    for at in atoms:
+        d = []
+        for a in range(3):
+            c = ax[a] - at[2 - a]
+            if per[a]:
+                c = c - SHAPE[a] * H * np.round(c / (SHAPE[a] * H))
+            d.append(c.reshape([-1 if b == a else 1 for b in range(3)]))
+        r = np.sqrt(d[0] ** 2 + d[1] ** 2 + d[2] ** 2)
+        t = (r - at[3]) / DELTA
+        u = 2.0 / (DELTA * np.sqrt(np.pi)) / erfcx(-t)            # h'/h
+        prod = prod * 0.5 * erfc(-t)
+        w = w + 2.0 * u / r - 2.0 * t * u / DELTA - u * u
+        for a in range(3):
+            g[a] = g[a] + u / r * d[a]
+    aH = (EPS0 - 1.0) * prod
+    g2 = g[0] ** 2 + g[1] ** 2 + g[2] ** 2
+    return aH + 1.0, 0.5 * aH * (g2 + w) - aH * aH * g2 / (4.0 * (aH + 1.0))
+
+
+@pytest.mark.parametrize("bc", ["free", "surface", "periodic", "wire"])
+@pytest.mark.parametrize("natoms", [1, 255, 256, 257, 600])
+def test_atom_lists(bc, natoms):
+    require_gpu()
+    atoms = _atoms(natoms, natoms)
+    ref_e, ref_q = _reference(atoms, bc)
+    p = plan(SHAPE, H, bc, "fp64")
+    e, q = empty(SHAPE), empty(SHAPE)
+    print("atom lists", bc, natoms, flush=True)
+    assert p.rigid_cavity(dev(atoms), DELTA, EPS0, e, q) == gps.GPS_OK
+    assert np.abs(host(e) - ref_e).max() <= 1e-13 * EPS0
+    assert np.abs(host(q) - ref_q).max() <= 1e-10 * np.abs(ref_q).max()
+
+
+@pytest.mark.parametrize("index", [0, 63, 255, 256, 599])
+@pytest.mark.parametrize("column,value", [(0, np.nan), (2, np.inf), (3, 0.0), (3, np.nan)])
+def test_bad_entry_refused_and_nothing_written(index, column, value):
+    require_gpu()
+    good = _atoms(600, 3)
+    bad = good.copy()
+    bad[index, column] = value
+    p = plan(SHAPE, H, "free", "fp64")
+    e, q = empty(SHAPE).fill_(-7.0), empty(SHAPE).fill_(-7.0)
+    print("bad atom", index, column, value, flush=True)
+    assert p.rigid_cavity(dev(bad), DELTA, EPS0, e, q) == gps.GPS_E_INVALID
+    assert (host(e) == -7.0).all() and (host(q) == -7.0).all()
+    assert p.rigid_cavity(dev(good), DELTA, EPS0, e, q) == gps.GPS_OK     # the flag is cleared
+    assert host(e).min() >= 1.0
