@@ -131,8 +131,16 @@ __global__ __launch_bounds__(kThreads) void k_rigid_cavity(Geom g, int nbx, int 
       const double r = sqrt(dx * dx + dy * dy + dz * dz);
       const double t = (r - at[3]) * idelta;
       if (t > kFarT) continue;
-      H *= 0.5 * erfc(-t);
-      const double u = cu / erfcx(-t);
+      // erfc(-t) and 1/erfcx(-t) from one erfcx and one exp, X = erfcx(|t|) and
+      // E = exp(-t^2) (the rounding of t^2 put back): erfc(|t|) = X E, and on the
+      // outside erfc(-t) = 2 - X E, 1/erfcx(-t) = E / erfc(-t)
+      const double X = erfcx(fabs(t));
+      const double t2 = t * t;
+      double E = exp(-t2);
+      E = fma(-fma(t, t, -t2), E, E);
+      const double c = t < 0.0 ? X * E : 2.0 - X * E;
+      H *= 0.5 * c;
+      const double u = t < 0.0 ? cu / X : cu * E / c;
       w -= 2.0 * t * u * idelta;
       if (r > 0.0) {
         const double ur = u / r;
