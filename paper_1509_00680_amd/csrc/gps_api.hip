@@ -190,7 +190,7 @@ struct gps_plan {
     size_t bytes = 0;
     hipGraphExec_t graphs[4] = {};
     int graph_iters[4] = {8, 4, 2, 1};
-    int graph_key = -1;           // paper_step + 2 (fd_order/2) + 64 (mixed)
+    int graph_key = -1;           // method + 4 (fd_order/2) + 64 (mixed)
   } sc;
   float* lap32t = nullptr;
   Res<float> r32;
@@ -999,8 +999,9 @@ gps_status solve_impl(gps_plan* pl, const double* rho, const double* eps, double
 // one vacuum solve (the plan's passes, bulk precision) of f = r/eps, the
 // operator A v = -4 pi r + eps grad ln eps . grad v with the two inner
 // products of the step, then the update phi += alpha v, r -= alpha A v (FP64)
-// with alpha taken on the device from the operator's partials, and a
-// one-work-group stop decision.  PSD takes Algorithm PCG's step with beta =
+// with alpha taken on the device from the operator's partials (one kernel for
+// SC, whose alpha is fixed), and a stop decision by one work-group of the next
+// step's y-inverse pass.  PSD takes Algorithm PCG's step with beta =
 // 0, (v, r)/(v, A v), and stops on ||r||_2; its weighted variant takes the
 // step that minimizes ||r/eps||_2, (A v, r/eps^2)/(A v, A v/eps^2), and stops
 // on ||r/eps||_2.  SC is the same recurrence with the fixed steps -1/(4 pi)
@@ -1035,8 +1036,10 @@ void ensure_sc(gps_plan* pl) {
 }
 
 // u = G f with the bulk-precision passes, enqueued on stream s (no wait).
+// sc: a stop decision taken beside the y inverse (SC/PSD steps).
 template <typename T>
-void enqueue_vacuum(gps_plan* pl, const double* f, double* u, hipStream_t s) {
+void enqueue_vacuum(gps_plan* pl, const double* f, double* u, hipStream_t s,
+                    const ScDecide& sc = ScDecide{}) {
   Res<T>& R = pl->res<T>();
   const Geom& g = pl->g;
   cplx<T>* work = R.slot().work;
@@ -1057,26 +1060,39 @@ void enqueue_vacuum(gps_plan* pl, const double* f, double* u, hipStream_t s) {
   SParams<T> yi = sparams<T>(pl, 1, g.Ly, g.Ly, g.ny, g.nz * g.Kx, g.Kx, (long long)g.Ly * g.Kx,
                              g.Kx);
   yi.work = work;
+  yi.sc = sc;
   launch_strided<T>(ST_INV, yi, s);
   launch_xinv<T>(XI_REAL, xp, s);
 }
 
-template <typename T>
-void enqueue_sc_step(gps_plan* pl, int paper_step, hipStream_t s) {
-  gps_plan::ScRes& S = pl->sc;
-  const long long n = pl->npts();
-  enqueue_vacuum<T>(pl, S.f, S.v, s);
-  // the operator launch also takes the previous step's stop decision
-  launch_sc_operator(pl->g, pl->opt.fd_order / 2, paper_step, S.r, S.eps, S.lne, S.v, S.av,
-                     S.part_op, &S.st->done, ScDecide{S.part, vec_groups(n), S.st}, s);
-  launch_sc_advance(n, S.eps, S.phi, S.r, S.v, S.av, S.f, S.part_op, polarization_groups(pl->g),
-                    S.part, S.st, s);
+// The partials that the stop decision of a step sums.
+ScDecide sc_decide_args(const gps_plan* pl, int method) {
+  const gps_plan::ScRes& S = pl->sc;
+  if (method == GPS_METHOD_SC) return ScDecide{S.part_op, polarization_groups(pl->g), S.st};
+  return ScDecide{S.part, vec_groups(pl->npts()), S.st};
 }
 
 template <typename T>
-void build_sc_graphs(gps_plan* pl, int paper_step) {
+void enqueue_sc_step(gps_plan* pl, int method, hipStream_t s) {
   gps_plan::ScRes& S = pl->sc;
-  const int key = paper_step + 2 * (pl->opt.fd_order / 2) + 64 * (sizeof(T) == sizeof(float));
+  const long long n = pl->npts();
+  // the y inverse also takes the previous step's stop decision
+  enqueue_vacuum<T>(pl, S.f, S.v, s, sc_decide_args(pl, method));
+  const int half = pl->opt.fd_order / 2;
+  if (method == GPS_METHOD_SC) {
+    launch_sc_step(pl->g, half, S.eps, S.lne, S.v, S.r, S.phi, S.f, S.part_op, S.st, s);
+    return;
+  }
+  launch_psd_operator(pl->g, half, method == GPS_METHOD_PSD, S.r, S.eps, S.lne, S.v, S.av,
+                      S.part_op, &S.st->done, s);
+  launch_psd_advance(n, S.eps, S.phi, S.r, S.v, S.av, S.f, S.part_op, polarization_groups(pl->g),
+                     S.part, S.st, s);
+}
+
+template <typename T>
+void build_sc_graphs(gps_plan* pl, int method) {
+  gps_plan::ScRes& S = pl->sc;
+  const int key = method + 4 * (pl->opt.fd_order / 2) + 64 * (sizeof(T) == sizeof(float));
   if (S.graphs[0] && S.graph_key == key) return;
   for (hipGraphExec_t& g : S.graphs) {
     if (g) (void)hipGraphExecDestroy(g);
@@ -1086,9 +1102,9 @@ void build_sc_graphs(gps_plan* pl, int paper_step) {
   std::lock_guard<std::mutex> lk(g_plan_mu);
   for (int i = 0; i < 4; ++i) {
     ck(hipStreamBeginCapture(pl->cap_stream, hipStreamCaptureModeThreadLocal));
-    for (int j = 0; j < S.graph_iters[i]; ++j) enqueue_sc_step<T>(pl, paper_step, pl->cap_stream);
+    for (int j = 0; j < S.graph_iters[i]; ++j) enqueue_sc_step<T>(pl, method, pl->cap_stream);
     // the last step's decision, so that the state read between replays is current
-    launch_sc_decide(ScDecide{S.part, vec_groups(pl->npts()), S.st}, pl->cap_stream);
+    launch_sc_decide(sc_decide_args(pl, method), pl->cap_stream);
     hipGraph_t graph = nullptr;
     const hipError_t e = hipStreamEndCapture(pl->cap_stream, &graph);
     if (e != hipSuccess) throw DevError{e};
@@ -1113,8 +1129,7 @@ gps_status sc_impl(gps_plan* pl, const double* rho, const double* eps, double* p
   gps_plan::ScRes& S = pl->sc;
   const long long n = pl->npts();
   hipStream_t s = pl->stream();
-  const int paper_step = method == GPS_METHOD_PSD;
-  build_sc_graphs<T>(pl, paper_step);
+  build_sc_graphs<T>(pl, method);
   const int max_steps = method == GPS_METHOD_SC ? pl->opt.maxit + 1 : pl->opt.maxit;
   launch_sc_begin(n, rho, eps, S.r, S.f, S.phi, S.eps, S.lne, S.part, S.st, method, eta, tol,
                   max_steps, s);

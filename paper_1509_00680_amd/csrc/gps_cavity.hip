@@ -12,6 +12,7 @@
 #include "gps.h"
 #include "gps_device.h"
 #include "gps_launch.h"
+#include "gps_sc.h"
 
 namespace gps {
 
@@ -39,7 +40,7 @@ namespace gps {
 // distance from the block's centre exceeds d + kFarT Delta by the half
 // diagonal is far from every point.  The other atoms used to cost every point
 // a square root and about 50 FP64 instructions: 96^3 points, 24 atoms in a ball of
-// 6 bohr: 40.1 -> @@K us.  The results are the same to the bit.
+// 6 bohr: 40.1 -> 27.5 us.  The results are the same to the bit.
 //
 // The atom table is checked here (finite centres, radii > 0), where every
 // work-group reads all of it anyway, instead of in a copy on the host: on a bad
@@ -173,47 +174,6 @@ void launch_rigid_cavity(const Geom& g, const double* atoms, int natoms, double 
 }
 
 // ---------------------------------------------------------------------------
-// Stop decision of an SC/PSD step (one work-group): from the update's partial
-// pairs (||r||^2, ||r/eps||^2) it records the step, its norms and the status,
-// and sets done on convergence, failure or the step limit.  It acts only when
-// the update has marked a decision pending, so every update is decided once,
-// whether by the next step's operator launch or by a launch of its own.
-// ---------------------------------------------------------------------------
-__device__ void sc_decide_group(const double* __restrict__ part, int nparts, ScState* st) {
-  if (st->done || !st->pending) return;          // the same for every thread
-  const double rr = sum_partials(part, nparts, 2);
-  const double ff = sum_partials(part + 1, nparts, 2);
-  if (threadIdx.x != 0) return;
-  ScState z = *st;
-  z.pending = 0;
-  if (z.status != GPS_E_NOT_CONVERGED) {          // breakdown or non-finite step
-    z.done = 1;
-    *st = z;
-    return;
-  }
-  const int step = z.step;
-  z.ff_prev = z.ff;
-  z.rr = rr;
-  z.ff = ff;
-  z.step = step + 1;
-  if (!isfinite(rr) || !isfinite(ff)) {
-    z.status = GPS_E_NONFINITE;
-  } else if (z.method == GPS_METHOD_SC) {
-    // SC's residual ||rho_iter_{k+1} - rho_iter_k|| = (eta/4 pi) ||r_k/eps|| of
-    // the iterate before this step; the first step is the unmixed phi_0
-    if (step >= 1) {
-      z.iters = step;
-      if (z.eta / kFourPi * sqrt(z.ff_prev) <= z.thr_sc) z.status = GPS_OK;
-    }
-  } else {
-    z.iters = step + 1;
-    if (z.method == GPS_METHOD_PSD ? sqrt(rr) <= z.thr_r : sqrt(ff) <= z.thr_w) z.status = GPS_OK;
-  }
-  if (z.status != GPS_E_NOT_CONVERGED || z.step >= z.max_steps) z.done = 1;
-  *st = z;
-}
-
-// ---------------------------------------------------------------------------
 // Polarization charge.  First differences of order 2M:
 //   f'(x) ~ (1/h) sum_{m=1..M} c_m (f(x + m h) - f(x - m h)),
 //   c_m = (-1)^(m+1) (M!)^2 / (m (M - m)! (M + m)!),
@@ -230,13 +190,24 @@ struct FdFirst { double c[9]; };
 constexpr int kPTX = 32, kPTY = 8;
 constexpr int kPThreads = kPTX * kPTY;
 
-// AV = false: out = rho_pol from (rho, eps, phi).  AV = true (PSD / SC
-// operator, Eq. PrePSD with grad eps = eps grad ln eps): with rho -> r and
-// phi -> v, out = A v = -4 pi r + eps grad ln eps . grad v, and two FP64
-// partials per work-group into part[2 b], part[2 b + 1]: (v, r) and (v, A v)
-// (paper != 0: Algorithm PCG's step with beta = 0), else (A v, r/eps^2) and
-// (A v, A v/eps^2) (the step that minimizes ||r/eps||_2).
-template <int M, bool AV>
+// What the stencil's grad lne . grad phi goes into:
+//   GD_POL   out = rho_pol from (rho, eps, phi).
+//   GD_PSD   the PSD operator (Eq. PrePSD with grad eps = eps grad ln eps): with
+//     rho -> r and phi -> v, out = A v = -4 pi r + eps grad ln eps . grad v, and two
+//     FP64 partials per work-group into part[2 b], part[2 b + 1]: (v, r) and
+//     (v, A v) (paper != 0: Algorithm PCG's step with beta = 0), else (A v, r/eps^2)
+//     and (A v, A v/eps^2) (the step that minimizes ||r/eps||_2).
+//   GD_SC    a whole step of Algorithm SC.  Its alpha is fixed, so A v is used where
+//     it is formed instead of being stored for an update kernel that reads five
+//     fields again: sol += alpha v, r -= alpha A v (in place), out = r/eps, and the
+//     partials ||r||^2, ||r/eps||^2.  96^3: operator 20.0 us + update 14.2 us -> 20.0 us together.
+enum GradDotMode { GD_POL = 0, GD_PSD = 1, GD_SC = 2 };
+struct ScStep {
+  double *r, *sol;          // GD_SC: residual and solution, updated in place
+  ScState* st;
+};
+
+template <int M, int MODE>
 __global__ __launch_bounds__(kPThreads) void k_polarization(Geom g, FdFirst w, int ntx, int nty,
                                                             int zlen, int paper, const int* stop,
                                                             const double* __restrict__ rho,
@@ -245,7 +216,7 @@ __global__ __launch_bounds__(kPThreads) void k_polarization(Geom g, FdFirst w, i
                                                             const double* __restrict__ phi,
                                                             double* __restrict__ out,
                                                             double* __restrict__ part,
-                                                            ScDecide dec) {
+                                                            ScStep sc) {
   constexpr int TW = kPTX + 2 * M;
   constexpr int TH = kPTY + 2 * M;
   constexpr int NXH = 2 * M * kPTY;                // halo slots left and right of the tile
@@ -253,17 +224,12 @@ __global__ __launch_bounds__(kPThreads) void k_polarization(Geom g, FdFirst w, i
   constexpr int HS = (NH + kPThreads - 1) / kPThreads;
   __shared__ double te[TH * TW];
   __shared__ double tp[TH * TW];
-  // SC/PSD: work-group 0 takes the previous update's stop decision, the
-  // tiles start at work-group 1
-  const int d0 = dec.st ? 1 : 0;
-  if (d0 && blockIdx.x == 0) {
-    sc_decide_group(dec.part, dec.nparts, dec.st);
-    return;
-  }
   if (stop && *stop) return;
+  double alpha = 0.0;
+  if constexpr (MODE == GD_SC) alpha = (sc.st->step == 0 ? -1.0 : -sc.st->eta) / kFourPi;
   const int tid = threadIdx.x;
   const int tx = tid % kPTX, ty = tid / kPTX;
-  const int t = xcd_tile(blockIdx.x - d0, gridDim.x - d0);   // x fastest, then y, then z chunk
+  const int t = xcd_tile(blockIdx.x, gridDim.x);   // x fastest, then y, then z chunk
   const int ntxy = ntx * nty;
   const int zc = t / ntxy;
   const int yt = (t - zc * ntxy) / ntx;
@@ -305,9 +271,9 @@ __global__ __launch_bounds__(kPThreads) void k_polarization(Geom g, FdFirst w, i
     he[s] = lne[(size_t)z0 * plane + ho[s]];
     hp[s] = phi[(size_t)z0 * plane + ho[s]];
   }
-  const double scale = AV ? 1.0 / (g.h * g.h) : 1.0 / (4.0 * kPi * g.h * g.h);
+  const double scale = MODE != GD_POL ? 1.0 / (g.h * g.h) : 1.0 / (4.0 * kPi * g.h * g.h);
   const bool inside = X < g.nx && Y < g.ny;
-  double vr = 0.0, vav = 0.0;
+  double p0 = 0.0, p1 = 0.0;                       // the two partials
   for (int z = z0; z < z1; ++z) {
     te[(M + ty) * TW + M + tx] = qe[M];
     tp[(M + ty) * TW + M + tx] = qp[M];
@@ -326,11 +292,12 @@ __global__ __launch_bounds__(kPThreads) void k_polarization(Geom g, FdFirst w, i
     }
     const size_t on = (size_t)ghost_index(z + 1 + M, g.nz, g.periodic_z) * plane + cxy;
     const double qne = lne[on], qnp = phi[on];
-    double rv = 0.0, ev = 1.0;
+    double rv = 0.0, ev = 1.0, sv = 0.0;
     const size_t o = (size_t)z * plane + (size_t)Y * g.nx + X;
     if (inside) {
-      rv = rho[o];
+      rv = MODE == GD_SC ? sc.r[o] : rho[o];
       ev = eps[o];
+      if constexpr (MODE == GD_SC) sv = sc.sol[o];
     }
     const double* ce = &te[(M + ty) * TW + M + tx];
     const double* cp = &tp[(M + ty) * TW + M + tx];
@@ -346,12 +313,21 @@ __global__ __launch_bounds__(kPThreads) void k_polarization(Geom g, FdFirst w, i
     }
     if (inside) {
       const double dot = (exd * pxd + eyd * pyd + ezd * pzd) * scale;
-      if constexpr (AV) {
+      if constexpr (MODE == GD_PSD) {
         const double av = -4.0 * kPi * rv + ev * dot;
         out[o] = av;
         const double aw = paper ? cp[0] : av / (ev * ev);
-        vr += aw * rv;
-        vav += aw * av;
+        p0 += aw * rv;
+        p1 += aw * av;
+      } else if constexpr (MODE == GD_SC) {
+        const double av = -4.0 * kPi * rv + ev * dot;
+        const double rn = rv - alpha * av;
+        const double fn = rn / ev;
+        sc.sol[o] = sv + alpha * cp[0];
+        sc.r[o] = rn;
+        out[o] = fn;
+        p0 += rn * rn;
+        p1 += fn * fn;
       } else {
         out[o] = dot - (1.0 - 1.0 / ev) * rv;
       }
@@ -370,12 +346,16 @@ __global__ __launch_bounds__(kPThreads) void k_polarization(Geom g, FdFirst w, i
       hp[s] = hnp[s];
     }
   }
-  if constexpr (AV) {
-    vr = block_sum(vr);
-    vav = block_sum(vav);
+  if constexpr (MODE != GD_POL) {
+    p0 = block_sum(p0);
+    p1 = block_sum(p1);
     if (tid == 0) {
-      part[2 * (blockIdx.x - d0)] = vr;
-      part[2 * (blockIdx.x - d0) + 1] = vav;
+      part[2 * blockIdx.x] = p0;
+      part[2 * blockIdx.x + 1] = p1;
+      if (MODE == GD_SC && blockIdx.x == 0) {
+        sc.st->alpha = alpha;
+        sc.st->pending = 1;
+      }
     }
   }
 }
@@ -445,18 +425,18 @@ void launch_log_field(long long n, const double* eps, double* lne, hipStream_t s
              n, eps, lne);
 }
 
-template <bool AV>
+template <int MODE>
 static void launch_graddot(const Geom& g, int fd_half, int paper, const double* rho,
                            const double* eps, const double* lne, const double* phi, double* out,
-                           double* part, const int* stop, const ScDecide& dec, hipStream_t s) {
+                           double* part, const int* stop, const ScStep& sc, hipStream_t s) {
   const int ntx = (g.nx + kPTX - 1) / kPTX, nty = (g.ny + kPTY - 1) / kPTY;
   const int zlen = polarization_zlen(g);
-  const dim3 grid(polarization_groups(g) + (dec.st ? 1 : 0));
+  const dim3 grid(polarization_groups(g));
   const FdFirst w = fd_first_weights(fd_half);
 #define GPS_PF(MM)                                                                        \
   case MM:                                                                                \
-    GPS_LAUNCH((k_polarization<MM, AV>), grid, dim3(kPThreads), 0, s, g, w, ntx, nty,     \
-               zlen, paper, stop, rho, eps, lne, phi, out, part, dec);                     \
+    GPS_LAUNCH((k_polarization<MM, MODE>), grid, dim3(kPThreads), 0, s, g, w, ntx, nty,   \
+               zlen, paper, stop, rho, eps, lne, phi, out, part, sc);                      \
     break;
   switch (fd_half) {
     GPS_PF(1) GPS_PF(2) GPS_PF(3) GPS_PF(4) GPS_PF(5) GPS_PF(6) GPS_PF(7) GPS_PF(8)
@@ -467,14 +447,20 @@ static void launch_graddot(const Geom& g, int fd_half, int paper, const double* 
 
 void launch_polarization(const Geom& g, int fd_half, const double* rho, const double* eps,
                          const double* lne, const double* phi, double* out, hipStream_t s) {
-  launch_graddot<false>(g, fd_half, 0, rho, eps, lne, phi, out, nullptr, nullptr, ScDecide{},
-                        s);
+  launch_graddot<GD_POL>(g, fd_half, 0, rho, eps, lne, phi, out, nullptr, nullptr, ScStep{}, s);
 }
 
-void launch_sc_operator(const Geom& g, int fd_half, int paper_step, const double* r,
-                        const double* eps, const double* lne, const double* v, double* av,
-                        double* part, const int* stop, const ScDecide& dec, hipStream_t s) {
-  launch_graddot<true>(g, fd_half, paper_step, r, eps, lne, v, av, part, stop, dec, s);
+void launch_psd_operator(const Geom& g, int fd_half, int paper_step, const double* r,
+                         const double* eps, const double* lne, const double* v, double* av,
+                         double* part, const int* stop, hipStream_t s) {
+  launch_graddot<GD_PSD>(g, fd_half, paper_step, r, eps, lne, v, av, part, stop, ScStep{}, s);
+}
+
+void launch_sc_step(const Geom& g, int fd_half, const double* eps, const double* lne,
+                    const double* v, double* r, double* phi, double* f, double* part,
+                    ScState* st, hipStream_t s) {
+  launch_graddot<GD_SC>(g, fd_half, 0, nullptr, eps, lne, v, f, part, &st->done,
+                        ScStep{r, phi, st}, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -544,7 +530,7 @@ __global__ __launch_bounds__(kThreads) void k_sc_start(const double* __restrict_
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_sc_update(long long n, const double* __restrict__ eps,
+__global__ __launch_bounds__(kThreads) void k_psd_update(long long n, const double* __restrict__ eps,
                                                         double* __restrict__ phi,
                                                         double* __restrict__ r,
                                                         const double* __restrict__ v,
@@ -557,16 +543,10 @@ __global__ __launch_bounds__(kThreads) void k_sc_update(long long n, const doubl
   // alpha, identical in every work-group (fixed-order sums of the operator's partials)
   const double vr = sum_partials(op_part, n_op, 2);
   const double vav = sum_partials(op_part + 1, n_op, 2);
-  const int method = st->method;
-  double alpha;
   int fail = 0;
-  if (method == GPS_METHOD_SC) {
-    alpha = (st->step == 0 ? -1.0 : -st->eta) / kFourPi;
-  } else {
-    if (!isfinite(vr) || !isfinite(vav)) fail = GPS_E_NONFINITE;
-    else if (method == GPS_METHOD_PSD ? vav == 0.0 : !(vav > 0.0)) fail = GPS_E_BREAKDOWN;
-    alpha = fail ? 0.0 : vr / vav;
-  }
+  if (!isfinite(vr) || !isfinite(vav)) fail = GPS_E_NONFINITE;
+  else if (st->method == GPS_METHOD_PSD ? vav == 0.0 : !(vav > 0.0)) fail = GPS_E_BREAKDOWN;
+  const double alpha = fail ? 0.0 : vr / vav;
   if (fail) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {   // the decision ends the solve
       st->status = fail;
@@ -632,11 +612,11 @@ void launch_sc_begin(long long n, const double* rho, const double* eps, double* 
              max_steps);
 }
 
-void launch_sc_advance(long long n, const double* eps, double* phi, double* r, const double* v,
+void launch_psd_advance(long long n, const double* eps, double* phi, double* r, const double* v,
                        const double* av, double* f, const double* op_part, int n_op,
                        double* part, ScState* st, hipStream_t s) {
   const int gv = vec_groups(n);
-  GPS_LAUNCH(k_sc_update, dim3(gv), dim3(kThreads), 0, s, n, eps, phi, r, v, av, f, op_part,
+  GPS_LAUNCH(k_psd_update, dim3(gv), dim3(kThreads), 0, s, n, eps, phi, r, v, av, f, op_part,
              n_op, part, st);
 }
 

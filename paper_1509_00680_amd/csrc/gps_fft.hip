@@ -14,6 +14,7 @@
 //            spectrum, C2C inverse, all in one pass through LDS.
 #include "gps_iter.h"
 #include "gps_launch.h"
+#include "gps_sc.h"
 
 namespace gps {
 
@@ -351,9 +352,10 @@ __global__ __launch_bounds__(kThreads) void k_strided(SParams<T> p) {
   const int tid = threadIdx.x;
   // y inverse of a solve: work-group 0 takes the stop decision, the tiles
   // start at work-group 1
-  const int dec = MODE == ST_INV ? p.decide : 0;
+  const int dec = MODE == ST_INV && (p.decide || p.sc.st) ? 1 : 0;
   if (MODE == ST_INV && dec && blockIdx.x == 0) {
-    pcg_decide(p.tab.s[p.batch.slot[blockIdx.y]], p.dec);
+    if (p.sc.st) sc_decide_group(p.sc.part, p.sc.nparts, p.sc.st);
+    else pcg_decide(p.tab.s[p.batch.slot[blockIdx.y]], p.dec);
     return;
   }
   cplx<T>* work = p.work;
@@ -466,7 +468,7 @@ template <typename T> int strided_parts(const SParams<T>& p) {
 
 template <typename T> void launch_strided(int mode, const SParams<T>& p, hipStream_t s) {
   if (fast_length(p.L) && fast_strided<T>(mode, p, s)) return;
-  const int dec = mode == ST_INV && p.decide ? 1 : 0;   // the decision work-group
+  const int dec = mode == ST_INV && (p.decide || p.sc.st) ? 1 : 0;   // the decision work-group
   const dim3 grid((p.npencils + p.B - 1) / p.B + dec, p.work ? 1 : p.batch.n);
   const size_t lds = (size_t)p.B * p.L * sizeof(cplx<T>);
   if (mode == ST_FWD) GPS_LAUNCH((k_strided<T, ST_FWD>), grid, dim3(kThreads), lds, s, p);

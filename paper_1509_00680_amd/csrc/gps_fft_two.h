@@ -21,6 +21,7 @@
 #include "gps_fft_reg.h"
 #include "gps_iter.h"
 #include "gps_launch.h"
+#include "gps_sc.h"
 
 namespace gps {
 
@@ -83,9 +84,10 @@ void k_fstrided(SParams<T> p) {
   // y inverse of a solve: work-group 0 only takes the stop decision (it runs
   // beside the transforms instead of after one); the tiles are numbered from
   // work-group 1 on
-  const int dec = MODE == ST_INV ? p.decide : 0;
+  const int dec = MODE == ST_INV && (p.decide || p.sc.st) ? 1 : 0;
   if (MODE == ST_INV && dec && blockIdx.x == 0) {
-    pcg_decide(p.tab.s[p.batch.slot[blockIdx.y]], p.dec);
+    if (p.sc.st) sc_decide_group(p.sc.part, p.sc.nparts, p.sc.st);
+    else pcg_decide(p.tab.s[p.batch.slot[blockIdx.y]], p.dec);
     return;
   }
   cplx<T>* work = p.work;
@@ -767,7 +769,7 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
   template <typename T, bool PAD>
   static void strided_p(int mode, const SParams<T>& p, hipStream_t s) {
     constexpr int B = strided_tile<T>(L);
-    const int dec = mode == ST_INV && p.decide ? 1 : 0;   // the decision work-group
+    const int dec = mode == ST_INV && (p.decide || p.sc.st) ? 1 : 0;   // the decision work-group
     constexpr int W = B * kStridedTiles;
     const dim3 grid((p.npencils + W - 1) / W + dec, p.work ? 1 : p.batch.n);
     if (mode == ST_FWD) strided_b<T, ST_FWD, PAD, B>(p, grid, s);

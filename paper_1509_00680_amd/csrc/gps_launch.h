@@ -32,6 +32,32 @@ LaunchEvents& launch_events();
     }                                                                                   \
   } while (0)
 
+// Device state of a solve by Algorithm SC or PSD (gps_solve_sc).
+struct ScState {
+  int done;          // 1 once the solve has stopped
+  int status;        // gps_status (GPS_E_NOT_CONVERGED while running)
+  int step;          // steps taken
+  int iters;         // iterations reported (SC: steps after the first)
+  int method;        // gps_sc_method
+  int max_steps;
+  int pending;       // 1 while the last update waits for its stop decision
+  double eta;        // SC mixing
+  double thr_w;      // tol ||4 pi rho / eps||
+  double thr_r;      // tol ||4 pi rho||
+  double thr_sc;     // tol ||rho||
+  double rr0;        // ||4 pi rho||^2
+  double rr;         // ||r||^2 after the last step
+  double ff;         // ||r/eps||^2 after the last step
+  double ff_prev;    // ||r/eps||^2 before the last step
+  double alpha;      // step of the last iteration
+};
+// Stop decision of an SC/PSD step from the update's partials (part, nparts
+// pairs); st == nullptr: none.
+struct ScDecide {
+  const double* part;
+  int nparts;
+  ScState* st;
+};
 // ---- FFT passes -----------------------------------------------------------
 
 // Pass along x: pairs of real rows -> one complex FFT of length Lx.
@@ -99,6 +125,8 @@ template <typename T> struct SParams {
   int plain_store;          // y forward, z pass over 32 MiB and more: ordinary stores (the output
                             // stays in the last-level cache for the next pass)
   DecideArgs dec;
+  ScDecide sc;              // ST_INV, explicit buffer: with sc.st, work-group 0 takes the
+                            // stop decision of the previous SC/PSD step
   cplx<T>* work;            // explicit buffer, or null to use the slots
   SlotTable<T> tab;
   Batch batch;
@@ -209,40 +237,18 @@ void launch_polarization(const Geom& g, int fd_half, const double* rho, const do
 int polarization_groups(const Geom& g);
 // Planes per z march of the 2.5D stencils over ntxy column tiles.
 int stencil_zlen(long long ntxy, int nz);
-// Device state of a solve by Algorithm SC or PSD (gps_solve_sc).
-struct ScState {
-  int done;          // 1 once the solve has stopped
-  int status;        // gps_status (GPS_E_NOT_CONVERGED while running)
-  int step;          // steps taken
-  int iters;         // iterations reported (SC: steps after the first)
-  int method;        // gps_sc_method
-  int max_steps;
-  int pending;       // 1 while the last update waits for its stop decision
-  double eta;        // SC mixing
-  double thr_w;      // tol ||4 pi rho / eps||
-  double thr_r;      // tol ||4 pi rho||
-  double thr_sc;     // tol ||rho||
-  double rr0;        // ||4 pi rho||^2
-  double rr;         // ||r||^2 after the last step
-  double ff;         // ||r/eps||^2 after the last step
-  double ff_prev;    // ||r/eps||^2 before the last step
-  double alpha;      // step of the last iteration
-};
-// Stop decision of an SC/PSD step from the update's partials (part, nparts
-// pairs); st == nullptr: none.
-struct ScDecide {
-  const double* part;
-  int nparts;
-  ScState* st;
-};
-// SC/PSD operator A v = -4 pi r + eps grad ln eps . grad v and two partials
+// PSD operator A v = -4 pi r + eps grad ln eps . grad v and two partials
 // per work-group (paper_step: (v, r) and (v, A v); else (A v, r/eps^2) and
-// (A v, A v/eps^2)); returns at once when *stop != 0 (stop may be null).  With
-// dec.st, one extra work-group takes the stop decision of the previous step's
-// update (if one is pending) while the others apply the operator.
-void launch_sc_operator(const Geom& g, int fd_half, int paper_step, const double* r,
-                        const double* eps, const double* lne, const double* v, double* av,
-                        double* part, const int* stop, const ScDecide& dec, hipStream_t s);
+// (A v, A v/eps^2)); returns at once when *stop != 0 (stop may be null).
+void launch_psd_operator(const Geom& g, int fd_half, int paper_step, const double* r,
+                         const double* eps, const double* lne, const double* v, double* av,
+                         double* part, const int* stop, hipStream_t s);
+// One step of Algorithm SC (fixed alpha): phi += alpha v, r -= alpha A v, f = r/eps,
+// with the ||r||^2, ||f||^2 partials of polarization_groups(g) work-groups, and the
+// step's stop decision marked pending.  Returns at once once the state says done.
+void launch_sc_step(const Geom& g, int fd_half, const double* eps, const double* lne,
+                    const double* v, double* r, double* phi, double* f, double* part,
+                    ScState* st, hipStream_t s);
 // The stop decision alone (the last update of a replayed chunk of steps).
 void launch_sc_decide(const ScDecide& dec, hipStream_t s);
 // Start of an SC/PSD solve: r = -4 pi rho, f = r/eps, phi = 0, eps_c = eps,
@@ -251,14 +257,13 @@ void launch_sc_decide(const ScDecide& dec, hipStream_t s);
 void launch_sc_begin(long long n, const double* rho, const double* eps, double* r, double* f,
                      double* phi, double* eps_c, double* lne, double* part, ScState* st,
                      int method, double eta, double tol, int max_steps, hipStream_t s);
-// The update of one SC/PSD step: every work-group takes alpha from the
+// The update of one PSD step: every work-group takes alpha from the
 // operator's n_op partial pairs, then phi += alpha v, r -= alpha A v, f =
 // r/eps with the ||r||^2, ||f||^2 partials, and marks the step's stop decision
-// pending (taken by the next operator launch or launch_sc_decide).  Returns
-// at once once the state says done.
-void launch_sc_advance(long long n, const double* eps, double* phi, double* r, const double* v,
-                       const double* av, double* f, const double* op_part, int n_op,
-                       double* part, ScState* st, hipStream_t s);
+// pending.  Returns at once once the state says done.
+void launch_psd_advance(long long n, const double* eps, double* phi, double* r, const double* v,
+                        const double* av, double* f, const double* op_part, int n_op,
+                        double* part, ScState* st, hipStream_t s);
 // (1/2) h^3 sum rho phi partials (one per work-group, stride 2) into part.
 void launch_sc_energy(long long n, const double* rho, const double* phi, double* part,
                       hipStream_t s);
