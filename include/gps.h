@@ -156,7 +156,7 @@ size_t gps_plan_device_bytes(const gps_plan *plan);
 
 /* Device bytes of a plan for an nx x ny x nz grid with boundary condition bc:
  * *tables, held from gps_plan_create to gps_plan_destroy (twiddles, Green's
- * spectrum); *buffers, the per-solve buffers that one solve in `precision`
+ * spectrum, and its copy in the plane pass's order for the grids that have one); *buffers, the per-solve buffers that one solve in `precision`
  * with iteration cap maxit allocates (nonlinear_pb != 0: a nonlinear
  * Poisson-Boltzmann solve, which adds the ionic-charge field; refine != 0:
  * true-residual refinement or warm start on, which adds their FP64 buffers) and
@@ -376,7 +376,8 @@ const char *gps_status_string(int status);
  * buffers if a resident plan has released them), fit in budget_bytes.  To make
  * room, idle plans release their buffers (gps_plan_release_buffers) and then
  * are destroyed, least recently used first in both steps.  Otherwise the request waits until
- * a running solve finishes.  Requests are taken in arrival order, except that
+ * a running solve finishes.  A request that alone exceeds the budget runs on a plan without
+ * the plane pass where that fits.  Requests are taken in arrival order, except that
  * a waiting request among the next 16 whose plan is resident and idle may go
  * ahead of older ones that need a new plan.  No request is passed over more
  * than 8 times.

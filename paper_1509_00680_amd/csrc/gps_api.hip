@@ -176,6 +176,13 @@ struct gps_plan {
   double* green64 = nullptr;
   float* green32 = nullptr;
   double* lap64t = nullptr;     // spectral Laplacian table (periodic)
+  // plane pass (FP32, FP64): shapes, and the Green's spectrum in its order; compact:
+  // made without it; no_half: its buffers did not fit, so the y, z, y passes run
+  PlaneShape shape32{}, shape64{};
+  double* plane64 = nullptr;
+  float* plane32 = nullptr;
+  bool compact = false;
+  bool no_half = false;
   double* pol_lne = nullptr;    // ln eps scratch of gps_polarization_charge (n doubles)
   size_t pol_bytes = 0;
   int* bad_atoms = nullptr;     // pinned: flag of gps_rigid_cavity's atom check
@@ -204,7 +211,13 @@ struct gps_plan {
   template <typename T> const T* green() const;
   template <typename T> const T* lap() const;
   template <typename T> const cplx<T>* tw(int axis) const;
+  template <typename T> const PlaneShape& shape() const;
+  template <typename T> const T* plane_table() const;
 };
+template <> const PlaneShape& gps_plan::shape<float>() const { return shape32; }
+template <> const PlaneShape& gps_plan::shape<double>() const { return shape64; }
+template <> const float* gps_plan::plane_table<float>() const { return plane32; }
+template <> const double* gps_plan::plane_table<double>() const { return plane64; }
 template <> Res<float>& gps_plan::res<float>() { return r32; }
 template <> Res<double>& gps_plan::res<double>() { return r64; }
 template <> const float* gps_plan::green<float>() const { return green32; }
@@ -382,6 +395,34 @@ void build_green(gps_plan* pl) {
   }
 }
 
+// The Green's spectrum in the plane pass's order, for each precision that has
+// one (so that the tables do not depend on the precision chosen later).
+size_t plane_table_count(const Geom& g) { return (size_t)g.Kx * g.Ly * (g.Lz / 2 + 1); }
+
+void build_plane_tables(gps_plan* pl) {
+  const Geom& g = pl->g;
+  if (pl->compact) return;
+  pl->shape32 = plane_shape(g, sizeof(float));
+  pl->shape64 = plane_shape(g, sizeof(double));
+  if (pl->shape32.N == 0 && pl->shape64.N == 0) return;
+  plane_allow_lds();
+  try {
+    if (pl->shape32.N > 0) {
+      dalloc(&pl->plane32, plane_table_count(g) * sizeof(float), &pl->bytes);
+      launch_plane_table(pl->shape32, pl->green64, g.Kx, g.Ly, pl->plane32, pl->cap_stream);
+    }
+    if (pl->shape64.N > 0) {
+      dalloc(&pl->plane64, plane_table_count(g) * sizeof(double), &pl->bytes);
+      launch_plane_table(pl->shape64, pl->green64, g.Kx, g.Ly, pl->plane64, pl->cap_stream);
+    }
+  } catch (const NoMem&) {               // the y, z, y passes need neither table
+    if (!pl->plane32) pl->shape32.N = 0;
+    if (!pl->plane64) pl->shape64.N = 0;
+  }
+  ck(hipGetLastError());
+  ck(hipStreamSynchronize(pl->cap_stream));
+}
+
 // ---------------------------------------------------------------------------
 // per-precision solve resources
 // ---------------------------------------------------------------------------
@@ -403,6 +444,13 @@ void alloc_slot(gps_plan* pl, Slot<T>& s, size_t* bytes) {
   if (pl->bc == GPS_BC_PERIODIC) dalloc(&s.s, nb, bytes);
   dalloc(&s.sq64, (size_t)n * sizeof(double), bytes);
   dalloc(&s.work, (size_t)g.nz * g.Ly * g.Kx * sizeof(cplx<T>), bytes);
+  if (pl->shape<T>().N > 0 && !pl->no_half) {
+    try {
+      dalloc(&s.half, (size_t)g.nz * g.ny * g.Kx * sizeof(cplx<T>), bytes);
+    } catch (const NoMem&) {
+      pl->no_half = true;
+    }
+  }
   dalloc(&s.part_init, (size_t)4 * nvg * sizeof(double), bytes);
   dalloc(&s.part_rr, (size_t)nxg * sizeof(double), bytes);
   dalloc(&s.part_delta, (size_t)nzg * sizeof(double), bytes);
@@ -416,7 +464,7 @@ void alloc_slot(gps_plan* pl, Slot<T>& s, size_t* bytes) {
 template <typename T>
 void free_slot(Slot<T>& s) {
   dfree(s.r); dfree(s.p); dfree(s.ap); dfree(s.isq); dfree(s.qk); dfree(s.s);
-  dfree(s.ion); dfree(s.sq64); dfree(s.work); dfree(s.part_init); dfree(s.part_rr);
+  dfree(s.ion); dfree(s.sq64); dfree(s.work); dfree(s.half); dfree(s.part_init); dfree(s.part_rr);
   dfree(s.part_delta); dfree(s.part_pap); dfree(s.part_mu); dfree(s.part_aux); dfree(s.hist);
   dfree(s.st); dfree(s.phi);
   dfree(s.sig64); dfree(s.src64); dfree(s.qk64);
@@ -584,9 +632,19 @@ double pass_bytes(const gps_plan* pl, int kind, size_t s) {
   switch (kind) {
     case GPS_K_XFWD: return (5.0 * s + 16.0) * n + rows * g.Kx * c;   // with the fused update
     case GPS_K_YFWD: return (double)g.nz * g.Kx * g.ny * c + wbox * c;
-    case GPS_K_ZCONV: return 2.0 * wbox * c + tab * s;
+    case GPS_K_ZCONV: {
+      const PlaneShape& sh = s == sizeof(float) ? pl->shape32 : pl->shape64;
+      if (sh.N > 0 && !pl->no_half)                   // plane pass
+        return (double)g.nz * g.ny * g.Kx * c + wbox * c +
+               (double)(g.Lz / 2 + 1) * g.Ly * g.Kx * s;
+      return 2.0 * wbox * c + tab * s;
+    }
     case GPS_K_YINV: return wbox * c + (double)g.nz * g.Kx * g.ny * c;
-    case GPS_K_XINV: return rows * g.Kx * c + (7.0 + periodic) * n * s;   // with the direction update
+    case GPS_K_XINV: {                                // with the direction update
+      const PlaneShape& sh = s == sizeof(float) ? pl->shape32 : pl->shape64;
+      const double in = sh.N > 0 && !pl->no_half ? wbox : rows * g.Kx;
+      return in * c + (7.0 + periodic) * n * s;
+    }
     default: return 0.0;
   }
 }
@@ -594,6 +652,27 @@ double pass_bytes(const gps_plan* pl, int kind, size_t s) {
 // ---------------------------------------------------------------------------
 // one PCG iteration for the problems of a batch (all of one plan)
 // ---------------------------------------------------------------------------
+// Whether the vacuum solver of this plan runs as x, plane, x.  A solve with
+// refinement keeps the y, z, y passes (its FP64 sources live in their x
+// passes), and so does a timed y pass.
+template <typename T>
+bool use_plane(const gps_plan* pl, int refine) {
+  return pl->shape<T>().N > 0 && !pl->no_half && !refine && pl->timing_kind != GPS_K_YFWD &&
+         pl->timing_kind != GPS_K_YINV;
+}
+
+template <typename T>
+PlaneParams<T> plane_params(const gps_plan* pl, const T* table) {
+  PlaneParams<T> p{};
+  p.sh = pl->shape<T>();
+  p.twy = pl->tw<T>(1);
+  p.twz = pl->tw<T>(2);
+  p.table = table;
+  p.Lx = pl->g.Lx;
+  p.Kx = pl->g.Kx;
+  return p;
+}
+
 template <typename T>
 void enqueue_iteration(gps_plan* pl, const SlotTable<T>& tab, const Batch& b, int check_neutral,
                        hipStream_t s, int k0, int refine) {
@@ -608,6 +687,24 @@ void enqueue_iteration(gps_plan* pl, const SlotTable<T>& tab, const Batch& b, in
   xp.refine = refine;
   check_parts(xp.n_pap_parts, part_caps(g).x);
   xp.periodic_mean = periodic;
+  if (use_plane<T>(pl, refine)) {
+    xp.sh = pl->shape<T>();
+      xp.dec.n_rr = xp.n_pap_parts;
+    xp.dec.n_delta = plane_groups(g.Kx);
+    check_parts(xp.dec.n_delta, part_caps(g).z);
+    xp.dec.n_init = vec_groups(n);
+    xp.dec.check_neutral = check_neutral;
+    xp.dec.periodic = periodic;
+    xp.dec.npts = double(n);
+    PlaneParams<T> pp = plane_params<T>(pl, pl->plane_table<T>());
+    pp.k0_from_slot = periodic;
+    pp.tab = tab;
+    pp.batch = b;
+    { TimerScope t(pl, s, GPS_K_XFWD, k0); launch_xfwd<T>(XF_SOLVE, xp, s); }
+    { TimerScope t(pl, s, GPS_K_ZCONV, k0); launch_plane<T>(pp, s); }
+    { TimerScope t(pl, s, GPS_K_XINV, k0); launch_xinv<T>(XI_SOLVE, xp, s); }
+    return;
+  }
   { TimerScope t(pl, s, GPS_K_XFWD, k0); launch_xfwd<T>(XF_SOLVE, xp, s); }
   SParams<T> yf = sparams<T>(pl, 1, g.Ly, g.ny, g.Ly, g.nz * g.Kx, g.Kx, (long long)g.Ly * g.Kx,
                              g.Kx);
@@ -686,18 +783,30 @@ void refine_step(gps_plan* pl, const double* rho, bool final_step) {
   ck(hipGetLastError());
 }
 
-// u = G f with the bulk-precision FFT passes (no sqrt(eps) scaling).
+// u = G f with the bulk-precision passes, enqueued on stream s (no wait).
+// sc: a stop decision taken beside the plane pass or the y inverse (SC/PSD steps).
 template <typename T>
-void vacuum_apply(gps_plan* pl, const double* f, double* u) {
-  ensure_res<T>(pl, false);
+void enqueue_vacuum(gps_plan* pl, const double* f, double* u, hipStream_t s,
+                    const ScDecide& sc = ScDecide{}) {
   Res<T>& R = pl->res<T>();
   const Geom& g = pl->g;
-  hipStream_t s = pl->stream();
   cplx<T>* work = R.slot().work;
   XParams<T> xp = xparams<T>(pl, g.ny * g.nz, g.ny, g.nx, g.nx, (long long)g.Ly * g.Kx, g.nx);
   xp.in_real = f;
   xp.out_real = u;
   xp.work = work;
+  if (use_plane<T>(pl, 0)) {
+    xp.sh = pl->shape<T>();
+      xp.half = R.slot().half;
+    PlaneParams<T> pp = plane_params<T>(pl, pl->plane_table<T>());
+    pp.half = xp.half;
+    pp.work = work;
+    pp.sc = sc;
+    launch_xfwd<T>(XF_REAL, xp, s);
+    launch_plane<T>(pp, s);
+    launch_xinv<T>(XI_REAL, xp, s);
+    return;
+  }
   launch_xfwd<T>(XF_REAL, xp, s);
   SParams<T> yf = sparams<T>(pl, 1, g.Ly, g.ny, g.Ly, g.nz * g.Kx, g.Kx, (long long)g.Ly * g.Kx,
                              g.Kx);
@@ -711,10 +820,18 @@ void vacuum_apply(gps_plan* pl, const double* f, double* u) {
   SParams<T> yi = sparams<T>(pl, 1, g.Ly, g.Ly, g.ny, g.nz * g.Kx, g.Kx, (long long)g.Ly * g.Kx,
                              g.Kx);
   yi.work = work;
+  yi.sc = sc;
   launch_strided<T>(ST_INV, yi, s);
   launch_xinv<T>(XI_REAL, xp, s);
+}
+
+// u = G f with the bulk-precision FFT passes (no sqrt(eps) scaling).
+template <typename T>
+void vacuum_apply(gps_plan* pl, const double* f, double* u) {
+  ensure_res<T>(pl, false);
+  enqueue_vacuum<T>(pl, f, u, pl->stream());
   ck(hipGetLastError());
-  ck(hipStreamSynchronize(s));
+  ck(hipStreamSynchronize(pl->stream()));
 }
 
 // Capture `chunk` PCG iterations as one graph (rebuilt when the variant
@@ -1033,36 +1150,6 @@ void ensure_sc(gps_plan* pl) {
       hipHostMalloc(reinterpret_cast<void**>(&S.h_part), (size_t)2 * gv * sizeof(double)) !=
           hipSuccess)
     throw NoMem{};
-}
-
-// u = G f with the bulk-precision passes, enqueued on stream s (no wait).
-// sc: a stop decision taken beside the y inverse (SC/PSD steps).
-template <typename T>
-void enqueue_vacuum(gps_plan* pl, const double* f, double* u, hipStream_t s,
-                    const ScDecide& sc = ScDecide{}) {
-  Res<T>& R = pl->res<T>();
-  const Geom& g = pl->g;
-  cplx<T>* work = R.slot().work;
-  XParams<T> xp = xparams<T>(pl, g.ny * g.nz, g.ny, g.nx, g.nx, (long long)g.Ly * g.Kx, g.nx);
-  xp.in_real = f;
-  xp.out_real = u;
-  xp.work = work;
-  launch_xfwd<T>(XF_REAL, xp, s);
-  SParams<T> yf = sparams<T>(pl, 1, g.Ly, g.ny, g.Ly, g.nz * g.Kx, g.Kx, (long long)g.Ly * g.Kx,
-                             g.Kx);
-  yf.work = work;
-  launch_strided<T>(ST_FWD, yf, s);
-  SParams<T> zc = sparams<T>(pl, 2, g.Lz, g.nz, g.nz, g.Ly * g.Kx, g.Ly * g.Kx, 0,
-                             (long long)g.Ly * g.Kx);
-  zc.work = work;
-  zc.table = pl->green<T>();
-  launch_strided<T>(ST_CONV, zc, s);
-  SParams<T> yi = sparams<T>(pl, 1, g.Ly, g.Ly, g.ny, g.nz * g.Kx, g.Kx, (long long)g.Ly * g.Kx,
-                             g.Kx);
-  yi.work = work;
-  yi.sc = sc;
-  launch_strided<T>(ST_INV, yi, s);
-  launch_xinv<T>(XI_REAL, xp, s);
 }
 
 // The partials that the stop decision of a step sums.
@@ -1475,6 +1562,8 @@ static void plan_release(gps_plan* pl) {
   dfree(pl->green32);
   dfree(pl->lap64t);
   dfree(pl->lap32t);
+  dfree(pl->plane64);
+  dfree(pl->plane32);
   dfree(pl->pol_lne);
   pl->pol_bytes = 0;
   if (pl->bad_atoms) (void)hipHostFree(pl->bad_atoms);
@@ -1482,23 +1571,8 @@ static void plan_release(gps_plan* pl) {
   free_sc(pl);
 }
 
-gps_status gps_plan_create(int nx, int ny, int nz, double h, int bc, gps_plan** out) {
-  if (!out) return GPS_E_INVALID;
-  *out = nullptr;
-  if (nx < 2 || ny < 2 || nz < 2 || !(h > 0.0) || !std::isfinite(h)) return GPS_E_INVALID;
-  if (bc != GPS_BC_FREE && bc != GPS_BC_SURFACE && bc != GPS_BC_PERIODIC && bc != GPS_BC_WIRE)
-    return GPS_E_INVALID;
-  gps_plan* pl = new (std::nothrow) gps_plan();
-  if (!pl) return GPS_E_NOMEM;
-  pl->bc = bc;
-  pl->opt.precision = GPS_PREC_FP64;
-  pl->opt.fd_order = 16;
-  pl->opt.maxit = 1000;
-  pl->opt.check_every = 4;
-  pl->opt.stream = nullptr;
-  pl->opt.refine_every = 0;
-  pl->opt.warm_start = 0;
-  Geom& g = pl->g;
+static Geom make_geom(int nx, int ny, int nz, double h, int bc) {
+  Geom g{};
   g.nx = nx;
   g.ny = ny;
   g.nz = nz;
@@ -1510,6 +1584,28 @@ gps_status gps_plan_create(int nx, int ny, int nz, double h, int bc, gps_plan** 
   g.Ly = g.periodic_y ? ny : 2 * ny;
   g.Lz = g.periodic_z ? nz : 2 * nz;
   g.Kx = g.Lx / 2 + 1;
+  return g;
+}
+
+static gps_status plan_create(int nx, int ny, int nz, double h, int bc, bool compact,
+                              gps_plan** out) {
+  if (!out) return GPS_E_INVALID;
+  *out = nullptr;
+  if (nx < 2 || ny < 2 || nz < 2 || !(h > 0.0) || !std::isfinite(h)) return GPS_E_INVALID;
+  if (bc != GPS_BC_FREE && bc != GPS_BC_SURFACE && bc != GPS_BC_PERIODIC && bc != GPS_BC_WIRE)
+    return GPS_E_INVALID;
+  gps_plan* pl = new (std::nothrow) gps_plan();
+  if (!pl) return GPS_E_NOMEM;
+  pl->bc = bc;
+  pl->compact = compact;
+  pl->opt.precision = GPS_PREC_FP64;
+  pl->opt.fd_order = 16;
+  pl->opt.maxit = 1000;
+  pl->opt.check_every = 4;
+  pl->opt.stream = nullptr;
+  pl->opt.refine_every = 0;
+  pl->opt.warm_start = 0;
+  const Geom& g = pl->g = make_geom(nx, ny, nz, h, bc);
   const int L[3] = {g.Lx, g.Ly, g.Lz};
   for (int a = 0; a < 3; ++a) {
     if (!factorize(L[a], &pl->rp[a])) {
@@ -1543,6 +1639,7 @@ gps_status gps_plan_create(int nx, int ny, int nz, double h, int bc, gps_plan** 
                         hipMemcpyHostToDevice, pl->cap_stream));
     }
     build_green(pl);   // synchronizes cap_stream (the host twiddles outlive the copies)
+    build_plane_tables(pl);
   } catch (const NoMem&) {
     plan_release(pl);
     delete pl;
@@ -1554,6 +1651,10 @@ gps_status gps_plan_create(int nx, int ny, int nz, double h, int bc, gps_plan** 
   }
   *out = pl;
   return GPS_OK;
+}
+
+gps_status gps_plan_create(int nx, int ny, int nz, double h, int bc, gps_plan** out) {
+  return plan_create(nx, ny, nz, h, bc, false, out);
 }
 
 gps_status gps_plan_set_options(gps_plan* pl, const gps_options* o) {
@@ -1586,12 +1687,13 @@ gps_status gps_plan_release_buffers(gps_plan* pl) {
   dfree(pl->pol_lne);
   pl->pol_bytes = 0;
   free_sc(pl);
+  pl->no_half = false;
   return GPS_OK;
 }
 
-gps_status gps_plan_footprint(int nx, int ny, int nz, int bc, int precision, int maxit,
-                              int nonlinear_pb, int refine, size_t* tables, size_t* buffers,
-                              size_t* transient) {
+static gps_status plan_footprint(int nx, int ny, int nz, int bc, int precision, int maxit,
+                                 int nonlinear_pb, int refine, bool compact, size_t* tables,
+                                 size_t* buffers, size_t* transient) {
   if (nx < 2 || ny < 2 || nz < 2 || maxit < 1) return GPS_E_INVALID;
   if (bc != GPS_BC_FREE && bc != GPS_BC_SURFACE && bc != GPS_BC_PERIODIC && bc != GPS_BC_WIRE)
     return GPS_E_INVALID;
@@ -1611,8 +1713,17 @@ gps_status gps_plan_footprint(int nx, int ny, int nz, int bc, int precision, int
   size_t tb = 2 * (Lx + Ly + Lz) * (sizeof(double) + sizeof(float));         // twiddles
   tb += ntab * (sizeof(double) + sizeof(float));                              // Green table
   if (pz) tb += ntab * (sizeof(double) + sizeof(float));                      // Laplacian table
+  size_t half = 0;                                                            // plane pass
+  if (!compact && Lx <= (size_t)kMaxLen && Ly <= (size_t)kMaxLen && Lz <= (size_t)kMaxLen) {
+    const Geom g = make_geom(nx, ny, nz, 1.0, bc);
+    const bool has32 = plane_shape(g, sizeof(float)).N > 0;
+    const bool has64 = plane_shape(g, sizeof(double)).N > 0;
+    const size_t np = (Lz / 2 + 1) * Ly * Kx;
+    tb += (has32 ? np * sizeof(float) : 0) + (has64 ? np * sizeof(double) : 0);
+    if (s == sizeof(float) ? has32 : has64) half = (size_t)nz * ny * Kx * 2 * s;
+  }
   size_t b = 5 * n * s + (pz ? n * s : 0) + n * sizeof(double);                     // vectors, sq64
-  b += wbox * 2 * s;                                                          // work buffer
+  b += wbox * 2 * s + half;                                                   // work buffers
   const size_t nzg = Ly * Kx + 64;
   b += (4 * nvg + 3 * nxg + nzg + (size_t)kVec * nvg) * sizeof(double);         // partials
   b += sizeof(SolveState) + n * sizeof(double);                               // state, phi
@@ -1628,6 +1739,13 @@ gps_status gps_plan_footprint(int nx, int ny, int nz, int bc, int precision, int
   if (buffers) *buffers = b;
   if (transient) *transient = t;
   return GPS_OK;
+}
+
+gps_status gps_plan_footprint(int nx, int ny, int nz, int bc, int precision, int maxit,
+                              int nonlinear_pb, int refine, size_t* tables, size_t* buffers,
+                              size_t* transient) {
+  return plan_footprint(nx, ny, nz, bc, precision, maxit, nonlinear_pb, refine, false, tables,
+                        buffers, transient);
 }
 
 void gps_plan_destroy(gps_plan* pl) {
@@ -1821,3 +1939,18 @@ gps_status gps_last_history(const gps_plan* pl, double* out, int max_entries) {
 }
 
 }  // extern "C"
+
+namespace gps {
+
+gps_status compact_plan_create(int nx, int ny, int nz, double h, int bc, gps_plan** out) {
+  return plan_create(nx, ny, nz, h, bc, true, out);
+}
+
+gps_status compact_plan_footprint(int nx, int ny, int nz, int bc, int precision, int maxit,
+                                  int nonlinear_pb, int refine, size_t* tables, size_t* buffers,
+                                  size_t* transient) {
+  return plan_footprint(nx, ny, nz, bc, precision, maxit, nonlinear_pb, refine, true, tables,
+                        buffers, transient);
+}
+
+}  // namespace gps

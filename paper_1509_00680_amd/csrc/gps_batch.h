@@ -33,6 +33,14 @@ struct BatchSlot {
   double rr0;         // ||r_0||^2
 };
 
+// A plan without the plane pass's table and buffers, and its footprint: as
+// gps_plan_create and gps_plan_footprint, for a memory budget that the whole
+// plan would exceed.  The same results to rounding.
+gps_status compact_plan_create(int nx, int ny, int nz, double h, int bc, gps_plan** out);
+gps_status compact_plan_footprint(int nx, int ny, int nz, int bc, int precision, int maxit,
+                                  int nonlinear_pb, int refine, size_t* tables, size_t* buffers,
+                                  size_t* transient);
+
 // Allocates nslots (1..kArgSlots) slots on the plan (bulk precision of its
 // options) and captures the batch graphs; check_neutral: periodic generalized
 // Poisson (input neutrality checked at the first decision).  Every slot

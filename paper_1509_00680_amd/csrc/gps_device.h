@@ -109,7 +109,8 @@ __device__ __forceinline__ V& at_bytes(V* base, unsigned off) {
 // pass (the stop decision), which it reads only at the end: so the flag is
 // the same for every wavefront of a launch, except in the y-inverse pass of
 // the last iteration, where the other work-groups' results are unused either
-// way.  stop_flag_issue is called right after
+// way.  (Beside the plane pass the x inverse holds the decision work-group; there
+// one thread's copy is broadcast to its work-group.)  stop_flag_issue is called right after
 // the pass's operand loads: every lane loads the flag through a vector load
 // (the zero offset comes from an instruction the compiler cannot fold), so it
 // travels with the operands and the wait for them covers it, instead of a

@@ -12,6 +12,9 @@
 //   y pass   strided C2C, in place in the work buffer.
 //   z pass   strided C2C forward, multiply by the real even Green's
 //            spectrum, C2C inverse, all in one pass through LDS.
+#include <algorithm>
+
+#include "gps_fft_plane.h"
 #include "gps_iter.h"
 #include "gps_launch.h"
 #include "gps_sc.h"
@@ -475,6 +478,126 @@ template <typename T> void launch_strided(int mode, const SParams<T>& p, hipStre
   else if (mode == ST_INV) GPS_LAUNCH((k_strided<T, ST_INV>), grid, dim3(kThreads), lds, s, p);
   else GPS_LAUNCH((k_strided<T, ST_CONV>), grid, dim3(kThreads), lds, s, p);
 }
+
+// ---------------------------------------------------------------------------
+// plane pass
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ void k_plane_table(PlaneShape sh, const double* __restrict__ t64, int Kx, int Ly,
+                              T* __restrict__ out) {
+  const int Lyh = Ly / 2 + 1, Lzh = sh.Lz / 2 + 1;
+  const long long n = (long long)Kx * kPlaneParts * Lzh * sh.N;
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
+       i += (long long)gridDim.x * blockDim.x) {
+    const int pos = (int)(i % sh.N);
+    const int kz = (int)((i / sh.N) % Lzh);
+    const int t = (int)(i / ((long long)sh.N * Lzh));
+    const int kx = t / kPlaneParts, r = t - kx * kPlaneParts;
+    const int a = pos / sh.A2, b = pos - a * sh.A2;      // k' = a + A1 b
+    const int ky = r + kPlaneParts * (a + sh.A1 * b);
+    out[i] = T(t64[((size_t)kz * Lyh + min(ky, Ly - ky)) * Kx + kx]);
+  }
+}
+
+template <typename T>
+void launch_plane_table(const PlaneShape& sh, const double* t64, int Kx, int Ly, T* out,
+                        hipStream_t s) {
+  const long long n = (long long)Kx * Ly * (sh.Lz / 2 + 1);
+  const int grid = (int)std::min<long long>((n + kThreads - 1) / kThreads, 65535);
+  GPS_LAUNCH((k_plane_table<T>), dim3(grid), dim3(kThreads), 0, s, sh, t64, Kx, Ly, out);
+}
+template void launch_plane_table<float>(const PlaneShape&, const double*, int, int, float*,
+                                        hipStream_t);
+template void launch_plane_table<double>(const PlaneShape&, const double*, int, int, double*,
+                                         hipStream_t);
+
+static bool plane_radix(int r) {
+  return (r >= 2 && r <= 10) || r == 12 || r == 14 || r == 15 || r == 16;
+}
+
+// n = a b over the codelets of the plane pass (b = 1 for n <= 5), the larger
+// factor as small as possible.  Along z (even: a padded axis) a is the larger, and
+// even; along y b is, the run of a row that neighbouring lanes load and store.
+static bool plane_split(int n, bool along_z, bool even, int* a, int* b) {
+  int best = 17;
+  for (int x = 2; x <= 16; ++x) {
+    if (n % x || !plane_radix(x) || (even && x % 2)) continue;
+    const int y = n / x;
+    if (y == 1 ? n > 5 : !plane_radix(y)) continue;
+    const int m = std::max(x, y);
+    if (m < best || (m == best && along_z)) {
+      best = m;
+      *a = x;
+      *b = y;
+    }
+  }
+  return best < 17;
+}
+
+// Dynamic LDS of the plane kernels: a CU's 160 KB less their static words.
+constexpr int kPlaneLds = 160 * 1024 - 512;
+
+// The plane pass runs where its tile fits one work-group's LDS (up to 96^3 free or
+// 128^3 periodic in FP32, 64^3 or 112^3 in FP64) and where the work-groups are
+// many enough for their size: lds <= 1100 per group.  Solves and vacuum solves of 70
+// random grids of 18 to 120 points: 1.01 to 1.20 x the y, z, y passes on this side
+// of the line (two FP64 grids at 0.996), 0.97 x beyond it (FP64, 105 x 108 x 70
+// periodic: 72 groups of 96 KB; 96^3 surface: 98 groups of 150 KB).
+PlaneShape plane_shape(const Geom& g, size_t elem) {
+  PlaneShape none{};
+  if (!fast_length(g.Lx) || g.Lx > kPlaneMaxLx || g.Ly % kPlaneParts) return none;
+  PlaneShape s{};
+  s.nz = g.nz;
+  s.ny = g.ny;
+  s.Lz = g.Lz;
+  s.N = g.Ly / kPlaneParts;
+  s.nm = g.ny / s.N;
+  s.padz = !g.periodic_z;
+  if (s.N < 2 || !plane_split(s.N, false, false, &s.A1, &s.A2) ||
+      !plane_split(s.Lz, true, s.padz, &s.C1, &s.C2) || s.C2 == 1)
+    return none;
+  s.PY = s.N | 1;                     // odd: the y steps' lanes run over z
+  s.lds = ((size_t)s.PY * s.Lz + s.Lz + 2 * s.N) * 2 * elem;
+  if (s.lds > (size_t)kPlaneLds || s.lds > 1100 * (size_t)plane_groups(g.Kx)) return none;
+  // threads: the count whose four kinds of steps take the fewest rounds, weighed
+  // by their lengths and about 8 more for a step's fixed work
+  const int jobs[4] = {s.nz * s.A2, s.nz * s.A1, s.N * s.C2, s.N * s.C1};
+  const int len[4] = {s.A1, s.A2, s.C1, s.C2};
+  double best = 1e30;
+  for (int nt = 64; nt <= plane_threads(elem); nt += 64) {
+    double cost = 0.002 * nt;
+    for (int i = 0; i < 4; ++i) cost += (double)((jobs[i] + nt - 1) / nt) * (len[i] + 8);
+    if (cost < best) {
+      best = cost;
+      s.threads = nt;
+    }
+  }
+  s.div_A2 = make_fastdiv((unsigned)s.A2);
+  s.div_nz = make_fastdiv((unsigned)s.nz);
+  s.div_N = make_fastdiv((unsigned)s.N);
+  s.div_ny = make_fastdiv((unsigned)s.ny);
+  return s;
+}
+
+void plane_allow_lds() {
+  const void* kernels[] = {
+      reinterpret_cast<const void*>(&k_plane<float, true>),
+      reinterpret_cast<const void*>(&k_plane<float, false>),
+      reinterpret_cast<const void*>(&k_plane<double, true>),
+      reinterpret_cast<const void*>(&k_plane<double, false>)};
+  for (const void* k : kernels)
+    if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kPlaneLds) != hipSuccess)
+      (void)hipGetLastError();
+}
+
+template <typename T> void launch_plane(const PlaneParams<T>& p, hipStream_t s) {
+  const dim3 grid(plane_groups(p.Kx) + (p.sc.st ? 1 : 0), p.work ? 1 : p.batch.n);
+  const dim3 blk(p.sh.threads);
+  if (p.sh.padz) GPS_LAUNCH((k_plane<T, true>), grid, blk, p.sh.lds, s, p);
+  else GPS_LAUNCH((k_plane<T, false>), grid, blk, p.sh.lds, s, p);
+}
+template void launch_plane<float>(const PlaneParams<float>&, hipStream_t);
+template void launch_plane<double>(const PlaneParams<double>&, hipStream_t);
 
 template int strided_parts<float>(const SParams<float>&);
 template int strided_parts<double>(const SParams<double>&);

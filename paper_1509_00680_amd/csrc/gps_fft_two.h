@@ -385,7 +385,10 @@ __device__ __forceinline__ void tile_row_offsets(const XParams<T>& p, int row0, 
   }
 }
 
-template <typename T, int L1, int L2, int P, int MODE, bool PAD>
+// PLANE: the half spectrum goes to one plane per kx, half[kx][row] (the input
+// of the plane pass): lanes run over the tile's rows, 2P consecutive values of
+// every plane.
+template <typename T, int L1, int L2, int P, int MODE, bool PAD, bool PLANE>
 __global__ __launch_bounds__(xthreads(L1, L2, P))
 void k_fxfwd(XParams<T> p) {
   constexpr bool SOLVE = MODE == XF_SOLVE || MODE == XF_SOLVE_REF;
@@ -529,22 +532,42 @@ void k_fxfwd(XParams<T> p) {
     for (int k2 = 0; k2 < L2; ++k2) lds[(q + L1 * k2) * PITCH + pp] = y[k2];
   }
   __syncthreads();
-  unsigned roff[2 * P];
-  bool rok[2 * P];
-  tile_row_offsets<2 * P>(p, row0, Kx, roff, rok);
+  if constexpr (PLANE) {
+    constexpr int KS = NT / P;                      // threads that share a row pair
+    cplx<T>* half = SOLVE ? sl.half : p.half;
+    const int ra = row0 + 2 * pp;
+    if (q < KS) {
 #pragma unroll
-  for (int p2 = 0; p2 < P; ++p2) {
+      for (int i = 0; i < (Kx + KS - 1) / KS; ++i) {
+        const int kk = q + i * KS;
+        if (kk < Kx) {
+          const cplx<T> zk = lds[kk * PITCH + pp];
+          const cplx<T> zm = lds[(kk == 0 ? 0 : L - kk) * PITCH + pp];
+          const T h = T(0.5);
+          const unsigned o = (unsigned)kk * (unsigned)p.nrows + (unsigned)ra;
+          if (ra < p.nrows) GPS_AT(half, o) = cmk(h * (zk.x + zm.x), h * (zk.y - zm.y));
+          if (ra + 1 < p.nrows) GPS_AT(half, o + 1) = cmk(h * (zk.y + zm.y), h * (zm.x - zk.x));
+        }
+      }
+    }
+  } else {
+    unsigned roff[2 * P];
+    bool rok[2 * P];
+    tile_row_offsets<2 * P>(p, row0, Kx, roff, rok);
 #pragma unroll
-    for (int i = 0; i < KI; ++i) {
-      const int kk = tid + i * NT;
-      if (kk < Kx) {
-        const cplx<T> zk = lds[kk * PITCH + p2];
-        const cplx<T> zm = lds[(kk == 0 ? 0 : L - kk) * PITCH + p2];
-        const T half = T(0.5);
-        if (rok[2 * p2])
-          GPS_AT(work, roff[2 * p2] + kk) = cmk(half * (zk.x + zm.x), half * (zk.y - zm.y));
-        if (rok[2 * p2 + 1])
-          GPS_AT(work, roff[2 * p2 + 1] + kk) = cmk(half * (zk.y + zm.y), half * (zm.x - zk.x));
+    for (int p2 = 0; p2 < P; ++p2) {
+#pragma unroll
+      for (int i = 0; i < KI; ++i) {
+        const int kk = tid + i * NT;
+        if (kk < Kx) {
+          const cplx<T> zk = lds[kk * PITCH + p2];
+          const cplx<T> zm = lds[(kk == 0 ? 0 : L - kk) * PITCH + p2];
+          const T half = T(0.5);
+          if (rok[2 * p2])
+            GPS_AT(work, roff[2 * p2] + kk) = cmk(half * (zk.x + zm.x), half * (zk.y - zm.y));
+          if (rok[2 * p2 + 1])
+            GPS_AT(work, roff[2 * p2 + 1] + kk) = cmk(half * (zk.y + zm.y), half * (zm.x - zk.x));
+        }
       }
     }
   }
@@ -576,7 +599,12 @@ void k_fxfwd(XParams<T> p) {
 // MODE XI_SOLVE / XI_SOLVE_PERIODIC / XI_SOLVE_REF: v = u / sqrt(eps) and the
 // direction update of the PCG iteration (with the periodic mean term; with the
 // refinement's sigma = r / sqrt(eps) + beta sigma); XI_REAL: plain output.
-template <typename T, int L1, int L2, int P, int MODE, bool PAD>
+// PLANE: the rows are the sums of the plane pass's two parities,
+//   row (z, y = j + m N) = work[kx][0][z][j] + (-1)^m work[kx][1][z][j],
+// read with lanes over the tile's rows; in a solve an extra work-group (the
+// first) takes the stop decision, and every work-group sums the plane pass's
+// delta partials for beta (a few hundred values, one per plane and parity).
+template <typename T, int L1, int L2, int P, int MODE, bool PAD, bool PLANE>
 __global__ __launch_bounds__(xthreads(L1, L2, P))
 void k_fxinv(XParams<T> p) {
   constexpr bool SOLVE = MODE != XI_REAL;
@@ -594,15 +622,34 @@ void k_fxinv(XParams<T> p) {
   __shared__ cplx<T> twl[L];
   const T* ldsr = reinterpret_cast<const T*>(lds);
   const int tid = threadIdx.x;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  constexpr int DEC = PLANE && SOLVE ? 1 : 0;      // the decision work-group
+  const Slot<T> sl = p.tab.s[p.batch.slot[blockIdx.y]];
+  if constexpr (DEC == 1) {
+    if (blockIdx.x == 0) {
+      pcg_decide(sl, p.dec);
+      return;
+    }
+  }
+  const int tile = xcd_tile(blockIdx.x, gridDim.x) - DEC;
   const int row0 = tile * 2 * P;
   cplx<T>* work = p.work;
-  const Slot<T> sl = p.tab.s[p.batch.slot[blockIdx.y]];
   if constexpr (SOLVE) work = sl.work;
   // the y-inverse decision of this iteration (plain loads: written by an
   // earlier kernel, first used in the epilogue)
   DirArgs dir{};
-  if constexpr (SOLVE) {
+  __shared__ int stopped;
+  constexpr int NPS = NT == 64 ? 16 : 8;
+  PartShare<DEC ? NPS : 4> sdl;
+  PartShare<DEC && PER ? NPS : 4> smu;
+  double dprev = 0.0;
+  if constexpr (DEC == 1) {
+    // (the decision work-group writes the other entry of delta only)
+    const int k = sl.st->k;
+    dir.fresh = k == 0;
+    dprev = sl.st->delta[(k - 1) & 1];
+    share_load(sdl, sl.part_delta, p.dec.n_delta);
+    if constexpr (PER) share_load(smu, sl.part_mu, p.dec.n_rr);
+  } else if constexpr (SOLVE) {
     dir.fresh = sl.st->fresh;
     dir.beta = sl.st->beta;
     dir.mu = PER ? sl.st->mu : 0.0;
@@ -612,20 +659,59 @@ void k_fxinv(XParams<T> p) {
 #pragma unroll
   for (int i = 0; i < ETW; ++i)
     twv[i] = load_parts(&p.tw[min(tid + i * NT, L - 1)]);   // clamped: no branch around the load
-  unsigned roff[2 * P];
-  bool rok[2 * P];
-  tile_row_offsets<2 * P>(p, row0, Kx, roff, rok);
-  cplx<T> xa[P][KI], xb[P][KI];
+  const int pp = tid % P;
+  const int q = tid / P;
+  constexpr int KS = NT / P;                       // PLANE: threads that share a row pair
+  constexpr int KP = (Kx + KS - 1) / KS;
+  cplx<T> xa[PLANE ? 1 : P][PLANE ? KP : KI], xb[PLANE ? 1 : P][PLANE ? KP : KI];
+  if constexpr (PLANE) {
+    cplx<T> ya[KP], yb[KP];
+    const unsigned N = (unsigned)p.sh.N, pstride = (unsigned)p.sh.nz * N;
+    unsigned off[2];
+    bool ok[2], minus[2];
 #pragma unroll
-  for (int p2 = 0; p2 < P; ++p2) {
+    for (int j = 0; j < 2; ++j) {
+      const int row = row0 + 2 * pp + j;
+      ok[j] = row < p.nrows;
+      const unsigned rc = ok[j] ? (unsigned)row : 0u;   // rows past the end read row 0
+      const unsigned z = fast_div(rc, p.sh.div_ny), y = rc - z * (unsigned)p.sh.ny;
+      minus[j] = y >= N;
+      off[j] = z * N + (minus[j] ? y - N : y);
+    }
 #pragma unroll
-    for (int i = 0; i < KI; ++i) {
-      const int kk = tid + i * NT;
-      const int kc = kk < Kx ? kk : Kx - 1;        // clamped: branch-free loads
-      const cplx<T> va = GPS_AT(work, roff[2 * p2] + kc);
-      const cplx<T> vb = GPS_AT(work, roff[2 * p2 + 1] + kc);
-      xa[p2][i] = rok[2 * p2] ? va : cmk(T(0), T(0));
-      xb[p2][i] = rok[2 * p2 + 1] ? vb : cmk(T(0), T(0));
+    for (int i = 0; i < KP; ++i) {
+      const int kk = q + i * KS;
+      const unsigned o = (unsigned)(kk < Kx ? kk : Kx - 1) * (2 * pstride);
+      xa[0][i] = GPS_AT(work, o + off[0]);
+      xb[0][i] = GPS_AT(work, o + off[1]);
+      ya[i] = GPS_AT(work, o + pstride + off[0]);
+      yb[i] = GPS_AT(work, o + pstride + off[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < KP; ++i) {
+      xa[0][i] = minus[0] ? csub(xa[0][i], ya[i]) : cadd(xa[0][i], ya[i]);
+      xb[0][i] = minus[1] ? csub(xb[0][i], yb[i]) : cadd(xb[0][i], yb[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < KP; ++i) {
+      if (!ok[0]) xa[0][i] = cmk(T(0), T(0));
+      if (!ok[1]) xb[0][i] = cmk(T(0), T(0));
+    }
+  } else {
+    unsigned roff[2 * P];
+    bool rok[2 * P];
+    tile_row_offsets<2 * P>(p, row0, Kx, roff, rok);
+#pragma unroll
+    for (int p2 = 0; p2 < P; ++p2) {
+#pragma unroll
+      for (int i = 0; i < KI; ++i) {
+        const int kk = tid + i * NT;
+        const int kc = kk < Kx ? kk : Kx - 1;        // clamped: branch-free loads
+        const cplx<T> va = GPS_AT(work, roff[2 * p2] + kc);
+        const cplx<T> vb = GPS_AT(work, roff[2 * p2 + 1] + kc);
+        xa[p2][i] = rok[2 * p2] ? va : cmk(T(0), T(0));
+        xb[p2][i] = rok[2 * p2 + 1] ? vb : cmk(T(0), T(0));
+      }
     }
   }
   // the stop flag right after the rows: the transform waits for both, and the
@@ -655,30 +741,38 @@ void k_fxinv(XParams<T> p) {
       if constexpr (PER) mv[i] = GPS_AT(sl.s, o);
       if constexpr (REF) gv[i] = GPS_AT(sl.sig64, o);
     }
-    if (stop_flag_set(stop)) return;
+    if constexpr (DEC == 0) {
+      if (stop_flag_set(stop)) return;
+    } else {
+      // the decision work-group may set the flag during this launch: one thread's
+      // copy, read after the staging's barrier, holds for the whole work-group
+      if (tid == 0) stopped = stop;
+    }
   }
 #pragma unroll
-  for (int p2 = 0; p2 < P; ++p2)
+  for (int p2 = 0; p2 < (PLANE ? 1 : P); ++p2)
 #pragma unroll
-  for (int i = 0; i < KI; ++i) {
-    const int kk = tid + i * NT;
-    if (kk < Kx) {
+  for (int i = 0; i < (PLANE ? KP : KI); ++i) {
+    const int kk = PLANE ? q + i * KS : tid + i * NT;
+    const int pr = PLANE ? pp : p2;                // row pair of the tile
+    if (kk < Kx && (!PLANE || q < KS)) {
       cplx<T> a = xa[p2][i], b = xb[p2][i];
       if (kk == 0 || 2 * kk == L) {    // self-conjugate bins of a real row
         a.y = T(0);
         b.y = T(0);
       }
-      lds[kk * PITCH + p2] = cmk(a.x - b.y, a.y + b.x);
+      lds[kk * PITCH + pr] = cmk(a.x - b.y, a.y + b.x);
       const int km = L - kk;
-      if (kk > 0 && km >= Kx) lds[km * PITCH + p2] = cmk(a.x + b.y, b.x - a.y);
+      if (kk > 0 && km >= Kx) lds[km * PITCH + pr] = cmk(a.x + b.y, b.x - a.y);
     }
   }
 #pragma unroll
   for (int i = 0; i < ETW; ++i)
     if (tid + i * NT < L) twl[tid + i * NT] = cmk(twv[i].x, twv[i].y);
   __syncthreads();
-  const int pp = tid % P;
-  const int q = tid / P;
+  if constexpr (DEC == 1) {
+    if (stopped) return;
+  }
   const cplx<T>* tw = twl;
   cplx<T> y[L2];
   if (q < L1) {
@@ -706,6 +800,11 @@ void k_fxinv(XParams<T> p) {
     for (int nb = 0; nb < L1; ++nb) lds[(q + L2 * nb) * PITCH + pp] = x[nb];
   }
   __syncthreads();
+  if constexpr (DEC == 1) {
+    const double delta = share_sum(sdl, sl.part_delta, p.dec.n_delta);
+    dir.beta = dir.fresh ? 0.0 : delta / dprev;
+    if constexpr (PER) dir.mu = share_sum(smu, sl.part_mu, p.dec.n_rr) / p.dec.npts;
+  }
   if constexpr (SOLVE) {
     double acc = 0.0;
     RowCol<Lout, NT> rc(tid);
@@ -792,33 +891,58 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
   }
 
   // The x passes exist for full rows (PAD = false) and for half-padded rows
-  // (PAD: L/2 points); with refinement on isolated axes' modes, and with the
-  // periodic mean term on full rows only (a padded x axis is not periodic).
+  // (PAD: L/2 points), the periodic mean term on full rows only (a padded x
+  // axis is not periodic); beside the plane pass there is no refinement.
   template <typename T, bool PAD>
   static void xfwd_p(int mode, const XParams<T>& p, dim3 grid, hipStream_t s) {
     const dim3 blk(xthreads(L1, L2, P));
-    if (mode == XF_SOLVE && p.refine)
-      GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_SOLVE_REF, PAD>), grid, blk, 0, s, p);
-    else if (mode == XF_SOLVE)
-      GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_SOLVE, PAD>), grid, blk, 0, s, p);
-    else
-      GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_REAL, PAD>), grid, blk, 0, s, p);
-  }
-  template <typename T, bool PAD>
-  static void xinv_p(int mode, const XParams<T>& p, dim3 grid, hipStream_t s) {
-    const dim3 blk(xthreads(L1, L2, P));
-    if constexpr (!PAD) {
-      if (mode == XI_SOLVE && p.periodic_mean) {
-        GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_SOLVE_PERIODIC, PAD>), grid, blk, 0, s, p);
+    if constexpr (L <= kPlaneMaxLx) {
+      if (p.sh.N > 0) {
+        if (mode == XF_SOLVE)
+          GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_SOLVE, PAD, true>), grid, blk, 0, s, p);
+        else
+          GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_REAL, PAD, true>), grid, blk, 0, s, p);
         return;
       }
     }
-    if (mode == XI_SOLVE && p.refine)
-      GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_SOLVE_REF, PAD>), grid, blk, 0, s, p);
-    else if (mode == XI_SOLVE)
-      GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_SOLVE, PAD>), grid, blk, 0, s, p);
+    if (mode == XF_SOLVE && p.refine) {
+      GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_SOLVE_REF, PAD, false>), grid, blk, 0, s, p);
+    } else if (mode == XF_SOLVE) {
+      GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_SOLVE, PAD, false>), grid, blk, 0, s, p);
+    } else {
+      GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_REAL, PAD, false>), grid, blk, 0, s, p);
+    }
+  }
+  template <typename T, bool PAD, bool PLANE>
+  static void xinv_m(int mode, const XParams<T>& p, dim3 grid, hipStream_t s) {
+    const dim3 blk(xthreads(L1, L2, P));
+    if constexpr (!PAD) {
+      if (mode == XI_SOLVE && p.periodic_mean) {
+        GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_SOLVE_PERIODIC, PAD, PLANE>), grid, blk, 0, s, p);
+        return;
+      }
+    }
+    if constexpr (!PLANE) {
+      if (mode == XI_SOLVE && p.refine) {
+        GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_SOLVE_REF, PAD, PLANE>), grid, blk, 0, s, p);
+        return;
+      }
+    }
+    if (mode == XI_SOLVE)
+      GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_SOLVE, PAD, PLANE>), grid, blk, 0, s, p);
     else
-      GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_REAL, PAD>), grid, blk, 0, s, p);
+      GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_REAL, PAD, PLANE>), grid, blk, 0, s, p);
+  }
+  template <typename T, bool PAD>
+  static void xinv_p(int mode, const XParams<T>& p, dim3 grid, hipStream_t s) {
+    if constexpr (L <= kPlaneMaxLx) {
+      if (p.sh.N > 0) {
+        if (mode == XI_SOLVE) grid.x += 1;             // the decision work-group
+        xinv_m<T, PAD, true>(mode, p, grid, s);
+        return;
+      }
+    }
+    xinv_m<T, PAD, false>(mode, p, grid, s);
   }
 
   template <typename T> static dim3 xgrid(const XParams<T>& p) {

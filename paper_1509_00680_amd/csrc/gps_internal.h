@@ -118,6 +118,7 @@ template <typename T> struct Slot {
   double *qk64;               // refinement: q + kappa2 in FP64 (null when off)
   double *sq64;               // sqrt(eps) in FP64 (stencil input)
   cplx<T> *work;              // FFT work buffer  nz * Ly * Kx
+  cplx<T> *half;              // plane pass: half spectrum along x, Kx planes of ny nz (or null)
   double *part_init;          // 4 partial sums per init work-group
   double *part_rr;            // ||r||^2 partials (x-forward work-groups)
   double *part_delta;         // (v, r) partials (z-pass work-groups)
@@ -145,6 +146,25 @@ struct Batch {
   int n;
   int slot[kArgSlots];        // index into the slot table
 };
+
+// Shape of the plane pass (gps_fft_plane.h): transforms of length N = Ly / 2 =
+// A1 A2 along y (one per parity of ky) and Lz = C1 C2 along z.  N = 0: the grid
+// takes the y, z, y passes.
+struct PlaneShape {
+  int N = 0;
+  int nm;                     // ny / N: blocks of a row that the fold adds (1 or 2)
+  int nz, ny, Lz;
+  int A1, A2, C1, C2;
+  int PY;                     // LDS pitch of a row of N elements
+  int threads;
+  int padz;
+  size_t lds;                 // bytes
+  FastDiv div_A2, div_nz, div_N, div_ny;
+};
+constexpr int kPlaneParts = 2;       // partial sums (parities of ky) of a plane
+constexpr int kPlaneMaxLx = 200;     // longest x length with passes beside the plane pass
+// Most threads of a plane-pass work-group: what its registers allow.
+constexpr int plane_threads(size_t elem) { return elem == 4 ? 768 : 512; }
 
 // Geometry of one plan, passed by value to kernels.
 struct Geom {

@@ -16,6 +16,10 @@
 //   x inverse   v_k; A v_k from the Eq. corr identity; p_k = v_k + beta p,
 //               Ap_k = A v_k + beta Ap; partials of (p_k, Ap_k).
 //
+// Grids with the plane pass (gps_fft_plane.h) run the y and z passes as one kernel;
+// its partials are of delta, and the x inverse's extra work-group takes the stop
+// decision while the others sum delta themselves for beta.
+//
 // Every scalar is a fixed-order FP64 sum of per-work-group partials, so a
 // solve's bits do not depend on timing.  Only work-group 0 writes the solve
 // state.

@@ -86,6 +86,12 @@ template <typename T> struct XParams {
   SlotTable<T> tab;
   int has_slots;
   Batch batch;
+  // plane pass (sh.N > 0): the x forward writes half[kx][row], the x inverse
+  // adds the two partial sums work[kx][r][z][j] and, in a solve, takes the stop
+  // decision in an extra work-group and beta in every work-group
+  PlaneShape sh;
+  cplx<T>* half;
+  DecideArgs dec;
   int n_pap_parts;          // (p, Ap) partials written by the x-inverse pass
   int periodic_mean;        // periodic: sum r/sqrt(eps) partials and the mean term
   int refine;               // track the FP64 sources sigma and s (true-residual refinement)
@@ -135,6 +141,31 @@ template <typename T> void launch_strided(int mode, const SParams<T>& p, hipStre
 // Partial sums written by a solve-mode z pass, whichever family runs (at most
 // the number of pencils plus 64).
 template <typename T> int strided_parts(const SParams<T>& p);
+
+// Plane pass: y forward, z and y inverse in one launch (gps_fft_plane.h).
+template <typename T> struct PlaneParams {
+  PlaneShape sh;
+  const cplx<T>* twy;       // twiddles of lengths Ly and Lz
+  const cplx<T>* twz;
+  const T* table;           // Green's spectrum in the pass's order (launch_plane_table)
+  int Lx, Kx;
+  int k0_from_slot;         // periodic: the k = 0 multiplier is the solve state's g0
+  ScDecide sc;              // with sc.st, work-group 0 takes an SC/PSD stop decision
+  const cplx<T>* half;      // explicit buffers, or null to use the slots
+  cplx<T>* work;
+  SlotTable<T> tab;
+  Batch batch;
+};
+// The plane pass of a grid (elem: bytes of the bulk type), N = 0 if it has none.
+PlaneShape plane_shape(const Geom& g, size_t elem);
+template <typename T> void launch_plane(const PlaneParams<T>& p, hipStream_t s);
+// Lets the plane kernels use a CU's whole LDS on the current device.
+void plane_allow_lds();
+inline int plane_groups(int Kx) { return kPlaneParts * Kx; }
+// Green's spectrum [kz][ky][kx] (folded) as [kx][r][kz folded][position of k'],
+// the order in which the pass's lanes read it.
+template <typename T> void launch_plane_table(const PlaneShape& sh, const double* t64, int Kx,
+                                              int Ly, T* out, hipStream_t s);
 
 // Two-level passes (gps_fft_two.h).  One entry per length that has them; a
 // length without an entry takes the generic passes.  The entries of

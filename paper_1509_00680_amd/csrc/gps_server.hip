@@ -37,8 +37,10 @@ constexpr int kServeChunk = 8;
 struct PlanKey {
   int nx, ny, nz, bc;
   double h;
+  bool compact;            // without the plane pass (the whole plan exceeds the budget)
   bool operator==(const PlanKey& o) const {
-    return nx == o.nx && ny == o.ny && nz == o.nz && bc == o.bc && h == o.h;
+    return nx == o.nx && ny == o.ny && nz == o.nz && bc == o.bc && h == o.h &&
+           compact == o.compact;
   }
 };
 
@@ -194,7 +196,9 @@ gps_status prepare_plan(gps_server* S, PlanEntry* e, const PlanKey& key, hipStre
                         int warm_start = 0, int refine_every = 0) {
   gps_status status = GPS_OK;
   if (!e->plan) {
-    status = gps_plan_create(key.nx, key.ny, key.nz, key.h, key.bc, &e->plan);
+    status = key.compact
+                 ? gps::compact_plan_create(key.nx, key.ny, key.nz, key.h, key.bc, &e->plan)
+                 : gps_plan_create(key.nx, key.ny, key.nz, key.h, key.bc, &e->plan);
     if (status != GPS_OK) e->plan = nullptr;
   }
   if (status == GPS_OK) {
@@ -556,7 +560,7 @@ gps_status gps_server_submit(gps_server* S, const gps_request* q, long long* tic
   Request* R = new (std::nothrow) Request();
   if (!R) return GPS_E_NOMEM;
   R->req = *q;
-  R->key = PlanKey{q->nx, q->ny, q->nz, q->bc, q->h};
+  R->key = PlanKey{q->nx, q->ny, q->nz, q->bc, q->h, false};
   if (q->ions) {
     const gps_ions& in = *q->ions;
     if (in.nspecies < 1 || in.nspecies > 4 || !in.Z || !in.c_bulk) {
@@ -593,9 +597,19 @@ gps_status gps_server_submit(gps_server* S, const gps_request* q, long long* tic
   R->batchable = S->opt.batch_slots > 1 && !nonlinear && !R->tracked &&
                  (long long)q->nx * q->ny * q->nz <= kBatchMaxPoints;
   if (R->batchable) R->buffers *= (size_t)S->opt.batch_slots;   // a plan of batch_slots slots
-  if (S->opt.budget_bytes && R->tables + R->buffers + R->transient > S->opt.budget_bytes) {
-    delete R;
-    return GPS_E_NOMEM;
+  const auto exceeds = [&] {
+    return S->opt.budget_bytes && R->tables + R->buffers + R->transient > S->opt.budget_bytes;
+  };
+  if (exceeds()) {                       // alone over the budget: without the plane pass
+    R->key.compact = true;
+    gps::compact_plan_footprint(q->nx, q->ny, q->nz, q->bc, S->opt.precision, S->opt.maxit,
+                                nonlinear, R->tracked ? 1 : 0, &R->tables, &R->buffers,
+                                &R->transient);
+    if (R->batchable) R->buffers *= (size_t)S->opt.batch_slots;
+    if (exceeds()) {
+      delete R;
+      return GPS_E_NOMEM;
+    }
   }
   std::lock_guard<std::mutex> lk(S->mu);
   R->ticket = S->next_ticket++;
