@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kThreads) void k_rigid_cavity(Geom g, int nbx, int 
       const double X = erfcx(fabs(t));
       const double t2 = t * t;
       double E = exp(-t2);
-      E = fma(-fma(t, t, -t2), E, E);
+      if (E > 0.0) E = fma(-fma(t, t, -t2), E, E);   // (t^2 may have overflowed where E is 0)
       const double c = t < 0.0 ? X * E : 2.0 - X * E;
       H *= 0.5 * c;
       const double u = t < 0.0 ? cu / X : cu * E / c;

@@ -76,3 +76,19 @@ def test_bad_entry_refused_and_nothing_written(index, column, value):
     assert (host(e) == -7.0).all() and (host(q) == -7.0).all()
     assert p.rigid_cavity(dev(good), DELTA, EPS0, e, q) == gps.GPS_OK     # the flag is cleared
     assert host(e).min() >= 1.0
+
+
+@pytest.mark.parametrize("delta", [1e-4, 1e-150, 1e-160, 1e-200])
+def test_sharp_surface(delta):
+    """A width far below the spacing: eps is 1 inside and eps0 outside, also where the square
+    of (r - d)/delta exceeds the largest double."""
+    require_gpu()
+    at = np.array([[0.1, 0.2, -0.3, 3.0]])
+    ax = [(np.arange(n) - (n - 1) / 2.0) * H - c for n, c in zip(SHAPE, at[0, 2::-1])]
+    r = np.sqrt(ax[0][:, None, None] ** 2 + ax[1][:, None] ** 2 + ax[2] ** 2)
+    assert np.abs(r - 3.0).min() > 30 * 1e-4
+    p = plan(SHAPE, H, "free", "fp64")
+    e = empty(SHAPE)
+    assert p.rigid_cavity(dev(at), delta, EPS0, e, None) == gps.GPS_OK
+    np.testing.assert_allclose(host(e), np.where(r < 3.0, 1.0, EPS0), rtol=1e-15)
+    p.close()
