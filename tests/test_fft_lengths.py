@@ -90,13 +90,14 @@ def test_strided_passes_in_bounds(L):
     assert n > 0
 
 
-@pytest.mark.parametrize("L", sorted(SPLITS))
-def test_x_pass_tiles_cover_the_rows(L):
+@pytest.mark.parametrize("L,few", [(L, False) for L in sorted(SPLITS)] +
+                         [(L, True) for L in (32, 48, 64)])
+def test_x_pass_tiles_cover_the_rows(L, few):
     """Every element of a tile is loaded by exactly one (thread, step), and the
     row and column the kernel advances by addition are those of the division."""
     L1, L2 = SPLITS[L]
     tuned = L in ib.FAST
-    P = ib.X_PAIRS(L1) if tuned else even_pairs(max(L1, L2))
+    P = 4 if few else ib.X_PAIRS(L1) if tuned else even_pairs(max(L1, L2))
     NT = ib.round64(P * max(L1, L2))
     assert NT <= 512
     for width in ((L // 2, L) if L % 2 == 0 else (L,)):

@@ -68,3 +68,30 @@ def test_solve_along_x(L):
                 bound = 1e-8 if precision == "fp64" else 1e-5
                 assert np.abs(err).max() <= bound * np.abs(ref.phi).max()
             p.close()
+
+
+@pytest.mark.parametrize("ny,nz", [(63, 63), (64, 64), (49, 84), (63, 75)])
+@pytest.mark.parametrize("n", [32, 48, 64])
+def test_row_pairs_by_row_count(n, ny, nz):
+    """Lengths 32, 48 and 64 take fewer row pairs per work-group up to 4096 rows: grids on both
+    sides of that line and on it, with full and partly filled last work-groups."""
+    require_gpu()
+    rng = np.random.default_rng(n)
+    shape, h = (nz, ny, n), 0.45
+    z, y, x = np.meshgrid(*[2.0 * np.pi * np.arange(m) / m for m in shape], indexing="ij")
+    eps = 6.0 + 2.0 * np.cos(x) * np.cos(y) + np.sin(z)
+    f = rng.normal(size=shape)
+    f -= f.mean()
+    expect = green.VacuumSolver(shape, h, "periodic").apply(f)
+    ref = pcg.pcg_solve(f, eps, h, "periodic", tol=1e-11)
+    lam = eps.min() * (2.0 * np.pi / (h * max(shape))) ** 2
+    for precision, vtol, stol in (("fp64", 1e-12, 1e-10), ("mixed", 3e-6, 1e-6)):
+        print("rows", shape, precision, flush=True)
+        p = plan(shape, h, "periodic", precision)
+        u, phi = empty(shape), empty(shape)
+        assert p.solve_vacuum(dev(f), u) == gps.GPS_OK
+        assert np.abs(host(u) - expect).max() <= vtol * np.abs(expect).max()
+        assert p.solve_generalized(dev(f), dev(eps), phi, stol) == gps.GPS_OK
+        err = np.linalg.norm(host(phi) - ref.phi)
+        assert err <= 2.0 * stol * 4.0 * np.pi * np.linalg.norm(f) / lam
+        p.close()
