@@ -156,7 +156,8 @@ size_t gps_plan_device_bytes(const gps_plan *plan);
 
 /* Device bytes of a plan for an nx x ny x nz grid with boundary condition bc:
  * *tables, held from gps_plan_create to gps_plan_destroy (twiddles, Green's
- * spectrum, and its copy in the plane pass's order for the grids that have one); *buffers, the per-solve buffers that one solve in `precision`
+ * spectrum, and its copy in the plane pass's order for the grids that have one);
+ * *buffers, the per-solve buffers that one solve in `precision`
  * with iteration cap maxit allocates (nonlinear_pb != 0: a nonlinear
  * Poisson-Boltzmann solve, which adds the ionic-charge field; refine != 0:
  * true-residual refinement or warm start on, which adds their FP64 buffers) and

@@ -633,16 +633,15 @@ double pass_bytes(const gps_plan* pl, int kind, size_t s) {
     case GPS_K_XFWD: return (5.0 * s + 16.0) * n + rows * g.Kx * c;   // with the fused update
     case GPS_K_YFWD: return (double)g.nz * g.Kx * g.ny * c + wbox * c;
     case GPS_K_ZCONV: {
-      const PlaneShape& sh = s == sizeof(float) ? pl->shape32 : pl->shape64;
-      if (sh.N > 0 && !pl->no_half)                   // plane pass
+      if (s == sizeof(float) && pl->shape32.N > 0 && !pl->no_half)   // plane pass
         return (double)g.nz * g.ny * g.Kx * c + wbox * c +
                (double)(g.Lz / 2 + 1) * g.Ly * g.Kx * s;
       return 2.0 * wbox * c + tab * s;
     }
     case GPS_K_YINV: return wbox * c + (double)g.nz * g.Kx * g.ny * c;
     case GPS_K_XINV: {                                // with the direction update
-      const PlaneShape& sh = s == sizeof(float) ? pl->shape32 : pl->shape64;
-      const double in = sh.N > 0 && !pl->no_half ? wbox : rows * g.Kx;
+      const bool plane = s == sizeof(float) && pl->shape32.N > 0 && !pl->no_half;
+      const double in = plane ? wbox : rows * g.Kx;
       return in * c + (7.0 + periodic) * n * s;
     }
     default: return 0.0;
@@ -654,7 +653,9 @@ double pass_bytes(const gps_plan* pl, int kind, size_t s) {
 // ---------------------------------------------------------------------------
 // Whether the vacuum solver of this plan runs as x, plane, x.  A solve with
 // refinement keeps the y, z, y passes (its FP64 sources live in their x
-// passes), and so does a timed y pass.
+// passes), and so does a timed y pass.  So do all FP64 PCG solves: PCG
+// multiplies a change of rounding by up to 1e8 (solutions of 32^3 to 64^3 at
+// 1e-6 differ by 1e-8), and FP64 results are to stay what they are.
 template <typename T>
 bool use_plane(const gps_plan* pl, int refine) {
   return pl->shape<T>().N > 0 && !pl->no_half && !refine && pl->timing_kind != GPS_K_YFWD &&
@@ -687,23 +688,25 @@ void enqueue_iteration(gps_plan* pl, const SlotTable<T>& tab, const Batch& b, in
   xp.refine = refine;
   check_parts(xp.n_pap_parts, part_caps(g).x);
   xp.periodic_mean = periodic;
-  if (use_plane<T>(pl, refine)) {
-    xp.sh = pl->shape<T>();
+  if constexpr (sizeof(T) == sizeof(float)) {
+    if (use_plane<T>(pl, refine)) {
+      xp.sh = pl->shape<T>();
       xp.dec.n_rr = xp.n_pap_parts;
-    xp.dec.n_delta = plane_groups(g.Kx);
-    check_parts(xp.dec.n_delta, part_caps(g).z);
-    xp.dec.n_init = vec_groups(n);
-    xp.dec.check_neutral = check_neutral;
-    xp.dec.periodic = periodic;
-    xp.dec.npts = double(n);
-    PlaneParams<T> pp = plane_params<T>(pl, pl->plane_table<T>());
-    pp.k0_from_slot = periodic;
-    pp.tab = tab;
-    pp.batch = b;
-    { TimerScope t(pl, s, GPS_K_XFWD, k0); launch_xfwd<T>(XF_SOLVE, xp, s); }
-    { TimerScope t(pl, s, GPS_K_ZCONV, k0); launch_plane<T>(pp, s); }
-    { TimerScope t(pl, s, GPS_K_XINV, k0); launch_xinv<T>(XI_SOLVE, xp, s); }
-    return;
+      xp.dec.n_delta = plane_groups(g.Kx);
+      check_parts(xp.dec.n_delta, part_caps(g).z);
+      xp.dec.n_init = vec_groups(n);
+      xp.dec.check_neutral = check_neutral;
+      xp.dec.periodic = periodic;
+      xp.dec.npts = double(n);
+      PlaneParams<T> pp = plane_params<T>(pl, pl->plane_table<T>());
+      pp.k0_from_slot = periodic;
+      pp.tab = tab;
+      pp.batch = b;
+      { TimerScope t(pl, s, GPS_K_XFWD, k0); launch_xfwd<T>(XF_SOLVE, xp, s); }
+      { TimerScope t(pl, s, GPS_K_ZCONV, k0); launch_plane<T>(pp, s); }
+      { TimerScope t(pl, s, GPS_K_XINV, k0); launch_xinv<T>(XI_SOLVE, xp, s); }
+      return;
+    }
   }
   { TimerScope t(pl, s, GPS_K_XFWD, k0); launch_xfwd<T>(XF_SOLVE, xp, s); }
   SParams<T> yf = sparams<T>(pl, 1, g.Ly, g.ny, g.Ly, g.nz * g.Kx, g.Kx, (long long)g.Ly * g.Kx,
@@ -797,7 +800,7 @@ void enqueue_vacuum(gps_plan* pl, const double* f, double* u, hipStream_t s,
   xp.work = work;
   if (use_plane<T>(pl, 0)) {
     xp.sh = pl->shape<T>();
-      xp.half = R.slot().half;
+    xp.half = R.slot().half;
     PlaneParams<T> pp = plane_params<T>(pl, pl->plane_table<T>());
     pp.half = xp.half;
     pp.work = work;

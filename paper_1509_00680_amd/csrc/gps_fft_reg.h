@@ -71,34 +71,53 @@ __host__ __device__ constexpr void ce_root(long long m, long long n, double* c, 
 }
 
 // cos and sin(2 pi m / N), m < N, evaluated by the front end.
-template <int N> struct RootTable {
+// KEPT: N = 8 and 16 with sqrt(1/2) and sin(pi/8) one unit in the last place below
+// the nearest double, as a binary64 series gave them first.  An FP64 PCG solve
+// multiplies a change of rounding by up to 1e8 before it reaches 1e-6 (solutions of
+// 32^3 to 64^3 differ by 1e-8), so the common lengths round as they always did.
+template <int N, bool KEPT> struct RootTable {
   double c[N], s[N];
+  static constexpr double kept(double v) {
+    constexpr double r[2] = {0.70710678118654757, 0.38268343236508978};
+    constexpr double k[2] = {0.70710678118654746, 0.38268343236508973};
+    for (int i = 0; i < 2; ++i) {
+      if (v == r[i]) return k[i];
+      if (v == -r[i]) return -k[i];
+    }
+    return v;
+  }
   constexpr RootTable() : c{}, s{} {
-    for (int m = 0; m < N; ++m) ce_root(m, N, &c[m], &s[m]);
+    for (int m = 0; m < N; ++m) {
+      ce_root(m, N, &c[m], &s[m]);
+      if (KEPT && (N == 8 || N == 16)) {
+        c[m] = kept(c[m]);
+        s[m] = kept(s[m]);
+      }
+    }
   }
 };
-template <int N> struct Roots2Pi { static constexpr RootTable<N> t{}; };
+template <int N, bool KEPT> struct Roots2Pi { static constexpr RootTable<N, KEPT> t{}; };
 
 // w_N^e = exp(-2 pi i e/N) (forward) or its conjugate (inverse), 0 <= e < N.
 // Called with indices that are constant after unrolling, so the table reads
 // fold to literals.
-template <typename T, int N, bool INV>
+template <typename T, int N, bool INV, bool KEPT>
 __device__ __forceinline__ cplx<T> croot(int e) {
-  const double c = Roots2Pi<N>::t.c[e], s = Roots2Pi<N>::t.s[e];
+  const double c = Roots2Pi<N, KEPT>::t.c[e], s = Roots2Pi<N, KEPT>::t.s[e];
   return cmk(T(c), T(INV ? s : -s));
 }
 
 // v * w_N^e for an exponent that is constant after unrolling: the quarter
 // turns (1, -1, -i, +i) become swaps and sign changes instead of a full
 // complex multiplication (whose products with 0 the compiler must keep).
-template <typename T, int N, bool INV>
+template <typename T, int N, bool INV, bool KEPT>
 __device__ __forceinline__ cplx<T> twiddle(cplx<T> v, int e) {
   e %= N;
   if (e == 0) return v;
   if (2 * e == N) return cmk(-v.x, -v.y);
   const bool minus_i = (4 * e == N) != INV;         // w = -i (else +i) when a quarter turn
   if (4 * e == N || 4 * e == 3 * N) return minus_i ? cmk(v.y, -v.x) : cmk(-v.y, v.x);
-  return cmul(v, croot<T, N, INV>(e));
+  return cmul(v, croot<T, N, INV, KEPT>(e));
 }
 
 // ---- small DFTs (radix butterflies) ---------------------------------------
@@ -170,11 +189,11 @@ __device__ __forceinline__ void rdft(cplx<T>* x) {
 }
 
 // ---- register Stockham over a compile-time radix list -----------------------
-template <typename T, bool INV, int N, int Ns, int... Rs> struct RegFFT {
+template <typename T, bool INV, bool KEPT, int N, int Ns, int... Rs> struct RegFFT {
   static __device__ __forceinline__ void run(cplx<T>*) {}
 };
-template <typename T, bool INV, int N, int Ns, int R, int... Rest>
-struct RegFFT<T, INV, N, Ns, R, Rest...> {
+template <typename T, bool INV, bool KEPT, int N, int Ns, int R, int... Rest>
+struct RegFFT<T, INV, KEPT, N, Ns, R, Rest...> {
   static __device__ __forceinline__ void run(cplx<T>* x) {
     cplx<T> y[N];
 #pragma unroll
@@ -184,7 +203,7 @@ struct RegFFT<T, INV, N, Ns, R, Rest...> {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         v[r] = x[j + r * (N / R)];
-        if (r > 0 && k > 0) v[r] = twiddle<T, Ns * R, INV>(v[r], r * k);
+        if (r > 0 && k > 0) v[r] = twiddle<T, Ns * R, INV, KEPT>(v[r], r * k);
       }
       rdft<T, INV, R>(v);
       const int base = (j / Ns) * Ns * R + k;
@@ -193,7 +212,7 @@ struct RegFFT<T, INV, N, Ns, R, Rest...> {
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) x[i] = y[i];
-    RegFFT<T, INV, N, Ns * R, Rest...>::run(x);
+    RegFFT<T, INV, KEPT, N, Ns * R, Rest...>::run(x);
   }
 };
 
@@ -217,9 +236,9 @@ template <int N1, int N2> struct PfaMap {
   static constexpr int E2 = N1 * ce_modinv(N1 % N2, N2);
 };
 
-template <typename T, bool INV, int N> struct Codelet;
+template <typename T, bool INV, int N, bool KEPT> struct Codelet;
 
-template <typename T, bool INV, int N1, int N2> struct PfaFFT {
+template <typename T, bool INV, int N1, int N2, bool KEPT> struct PfaFFT {
   static __device__ __forceinline__ void run(cplx<T>* x) {
     constexpr int N = N1 * N2;
     cplx<T> y[N];
@@ -228,7 +247,7 @@ template <typename T, bool INV, int N1, int N2> struct PfaFFT {
       cplx<T> v[N1];
 #pragma unroll
       for (int n1 = 0; n1 < N1; ++n1) v[n1] = x[(N2 * n1 + N1 * n2) % N];
-      Codelet<T, INV, N1>::run(v);
+      Codelet<T, INV, N1, KEPT>::run(v);
 #pragma unroll
       for (int k1 = 0; k1 < N1; ++k1) y[k1 * N2 + n2] = v[k1];
     }
@@ -237,7 +256,7 @@ template <typename T, bool INV, int N1, int N2> struct PfaFFT {
       cplx<T> v[N2];
 #pragma unroll
       for (int n2 = 0; n2 < N2; ++n2) v[n2] = y[k1 * N2 + n2];
-      Codelet<T, INV, N2>::run(v);
+      Codelet<T, INV, N2, KEPT>::run(v);
 #pragma unroll
       for (int k2 = 0; k2 < N2; ++k2)
         x[(k1 * PfaMap<N1, N2>::E1 + k2 * PfaMap<N1, N2>::E2) % N] = v[k2];
@@ -248,15 +267,15 @@ template <typename T, bool INV, int N1, int N2> struct PfaFFT {
 // Radix lists of the codelet lengths (prime-factor form where N splits into
 // coprime factors).
 #define GPS_CODELET(N, ...)                                                         \
-  template <typename T, bool INV> struct Codelet<T, INV, N> {                       \
+  template <typename T, bool INV, bool KEPT> struct Codelet<T, INV, N, KEPT> {      \
     static __device__ __forceinline__ void run(cplx<T>* x) {                        \
-      RegFFT<T, INV, N, 1, __VA_ARGS__>::run(x);                                    \
+      RegFFT<T, INV, KEPT, N, 1, __VA_ARGS__>::run(x);                              \
     }                                                                               \
   };
 #define GPS_PFA_CODELET(N, N1, N2)                                                  \
-  template <typename T, bool INV> struct Codelet<T, INV, N> {                       \
+  template <typename T, bool INV, bool KEPT> struct Codelet<T, INV, N, KEPT> {      \
     static __device__ __forceinline__ void run(cplx<T>* x) {                        \
-      PfaFFT<T, INV, N1, N2>::run(x);                                               \
+      PfaFFT<T, INV, N1, N2, KEPT>::run(x);                                         \
     }                                                                               \
   };
 GPS_CODELET(2, 2)
@@ -282,9 +301,9 @@ GPS_PFA_CODELET(28, 4, 7)
 #undef GPS_PFA_CODELET
 
 // Natural-order DFT of N values held in registers.
-template <typename T, bool INV, int N>
+template <typename T, bool INV, int N, bool KEPT = false>
 __device__ __forceinline__ void reg_fft(cplx<T>* x) {
-  Codelet<T, INV, N>::run(x);
+  Codelet<T, INV, N, KEPT>::run(x);
 }
 
 }  // namespace gps

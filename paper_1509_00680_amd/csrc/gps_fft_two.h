@@ -40,6 +40,11 @@ template <typename T> constexpr int strided_tile(int L) {
 }
 constexpr int round64(int v) { return (v + 63) / 64 * 64; }
 constexpr int larger(int a, int b) { return a > b ? a : b; }
+// The tuned lengths keep their first constants (Roots2Pi); the others take the nearest.
+constexpr bool kept_roots(int L) {
+  return L == 32 || L == 48 || L == 64 || L == 96 || L == 128 || L == 192 || L == 256 ||
+         L == 320 || L == 384;
+}
 
 template <typename T>
 __device__ __forceinline__ cplx<T> cconj(cplx<T> a) { return cmk(a.x, -a.y); }
@@ -232,7 +237,7 @@ void k_fstrided(SParams<T> p) {
         cplx<T> x[L1];
 #pragma unroll
         for (int n1 = 0; n1 < L1; ++n1) x[n1] = xin[t][n1];
-        reg_fft<T, false, L1>(x);
+        reg_fft<T, false, L1, kept_roots(L1 * L2)>(x);
 #pragma unroll
         for (int k1 = 1; k1 < L1; ++k1) x[k1] = cmul(x[k1], tw[q * k1]);
 #pragma unroll
@@ -242,7 +247,7 @@ void k_fstrided(SParams<T> p) {
       if (q < L1) {
 #pragma unroll
         for (int n2 = 0; n2 < L2; ++n2) y[n2] = lds[(n2 * L1 + q) * PITCH + b];
-        reg_fft<T, false, L2>(y);               // y[k2] = X[q + L1 k2]
+        reg_fft<T, false, L2, kept_roots(L1 * L2)>(y);               // y[k2] = X[q + L1 k2]
       }
       if constexpr (MODE == ST_FWD) {
         if (pv[t] && q < L1) {
@@ -288,7 +293,7 @@ void k_fstrided(SParams<T> p) {
     }
     // inverse transform (ST_CONV second half, ST_INV)
     if (q < L1) {
-      reg_fft<T, true, L2>(y);                  // y[n_a] = Z[q][n_a]
+      reg_fft<T, true, L2, kept_roots(L1 * L2)>(y);                  // y[n_a] = Z[q][n_a]
 #pragma unroll
       for (int na = 1; na < L2; ++na) y[na] = cmul(y[na], cconj(tw[na * q]));
 #pragma unroll
@@ -299,7 +304,7 @@ void k_fstrided(SParams<T> p) {
       cplx<T> x[L1];
 #pragma unroll
       for (int k1 = 0; k1 < L1; ++k1) x[k1] = lds[(q * L1 + k1) * PITCH + b];
-      reg_fft<T, true, L1>(x);                  // x[n_b] = out[q + L2 n_b]
+      reg_fft<T, true, L1, kept_roots(L1 * L2)>(x);                  // x[n_b] = out[q + L2 n_b]
       if (pv[t]) {
         auto store = [&](auto plain) {
 #pragma unroll
@@ -510,7 +515,7 @@ void k_fxfwd(XParams<T> p) {
   if (q < L2) {
 #pragma unroll
     for (int n1 = 0; n1 < L1; ++n1) x[n1] = lds[(L2 * n1 + q) * PITCH + pp];
-    reg_fft<T, false, L1>(x);
+    reg_fft<T, false, L1, kept_roots(L1 * L2)>(x);
 #pragma unroll
     for (int k1 = 1; k1 < L1; ++k1) x[k1] = cmul(x[k1], tw[q * k1]);
   }
@@ -524,7 +529,7 @@ void k_fxfwd(XParams<T> p) {
   if (q < L1) {
 #pragma unroll
     for (int n2 = 0; n2 < L2; ++n2) y[n2] = lds[(n2 * L1 + q) * PITCH + pp];
-    reg_fft<T, false, L2>(y);
+    reg_fft<T, false, L2, kept_roots(L1 * L2)>(y);
   }
   __syncthreads();
   if (q < L1) {
@@ -778,7 +783,7 @@ void k_fxinv(XParams<T> p) {
   if (q < L1) {
 #pragma unroll
     for (int k2 = 0; k2 < L2; ++k2) y[k2] = lds[(q + L1 * k2) * PITCH + pp];
-    reg_fft<T, true, L2>(y);
+    reg_fft<T, true, L2, kept_roots(L1 * L2)>(y);
 #pragma unroll
     for (int na = 1; na < L2; ++na) y[na] = cmul(y[na], cconj(tw[na * q]));
   }
@@ -792,7 +797,7 @@ void k_fxinv(XParams<T> p) {
   if (q < L2) {
 #pragma unroll
     for (int k1 = 0; k1 < L1; ++k1) x[k1] = lds[(q * L1 + k1) * PITCH + pp];
-    reg_fft<T, true, L1>(x);
+    reg_fft<T, true, L1, kept_roots(L1 * L2)>(x);
   }
   __syncthreads();
   if (q < L2) {
@@ -892,16 +897,20 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
 
   // The x passes exist for full rows (PAD = false) and for half-padded rows
   // (PAD: L/2 points), the periodic mean term on full rows only (a padded x
-  // axis is not periodic); beside the plane pass there is no refinement.
+  // axis is not periodic); beside the plane pass there is no refinement
+  // and no FP64 solve.
   template <typename T, bool PAD>
   static void xfwd_p(int mode, const XParams<T>& p, dim3 grid, hipStream_t s) {
     const dim3 blk(xthreads(L1, L2, P));
     if constexpr (L <= kPlaneMaxLx) {
       if (p.sh.N > 0) {
-        if (mode == XF_SOLVE)
-          GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_SOLVE, PAD, true>), grid, blk, 0, s, p);
-        else
-          GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_REAL, PAD, true>), grid, blk, 0, s, p);
+        if constexpr (sizeof(T) == sizeof(float)) {
+          if (mode == XF_SOLVE) {
+            GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_SOLVE, PAD, true>), grid, blk, 0, s, p);
+            return;
+          }
+        }
+        GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_REAL, PAD, true>), grid, blk, 0, s, p);
         return;
       }
     }
@@ -916,6 +925,10 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
   template <typename T, bool PAD, bool PLANE>
   static void xinv_m(int mode, const XParams<T>& p, dim3 grid, hipStream_t s) {
     const dim3 blk(xthreads(L1, L2, P));
+    if constexpr (PLANE && sizeof(T) != sizeof(float)) {
+      GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_REAL, PAD, PLANE>), grid, blk, 0, s, p);
+      return;
+    }
     if constexpr (!PAD) {
       if (mode == XI_SOLVE && p.periodic_mean) {
         GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_SOLVE_PERIODIC, PAD, PLANE>), grid, blk, 0, s, p);
