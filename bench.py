@@ -121,10 +121,10 @@ def copy_calibration(mib):
     print(json.dumps({"copy_calibration_mib": mib, "copies": 10}))
 
 
-# the translation unit of the FFT passes (the kernels whose counters are
-# recorded): their source file and every header it includes
-FFT_PASS_SOURCES = ("gps_fft_fast.hip", "gps_fft_two.h", "gps_fft_reg.h", "gps_iter.h", "gps_launch.h",
-                    "gps_device.h", "gps_internal.h")
+# the sources of the two-level and plane passes (the kernels whose counters are
+# recorded), with every header they include
+FFT_PASS_SOURCES = ("gps_fft_fast.hip", "gps_fft_two.h", "gps_fft_plane.h", "gps_fft_reg.h",
+                    "gps_sc.h", "gps_iter.h", "gps_launch.h", "gps_device.h", "gps_internal.h")
 
 
 def kernel_source_digest():
@@ -599,7 +599,8 @@ def pcg_line(args, torch, gps, W, prob, name, steps, warmup, cpu=True, pass_time
         "energy": info["energy"],
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(traffic_file),
-                     "kernel": "z pass (forward FFT, Green's spectrum, inverse FFT)",
+                     "kernel": "z pass (forward FFT, Green's spectrum, inverse FFT), or the plane pass "
+                               "(y forward, the z pass, y inverse) on grids that take it",
                      "avg_us": avg_ms * 1e3, "bytes_per_launch": tz["bytes_per_launch"],
                      "launches": tz["launches"]},
         "fp64_one_at_a_time": fp64,
