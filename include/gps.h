@@ -163,7 +163,9 @@ size_t gps_plan_device_bytes(const gps_plan *plan);
  * true-residual refinement or warm start on, which adds their FP64 buffers) and
  * gps_plan_release_buffers frees; *transient, held only while gps_plan_create
  * builds the Green's spectrum (FP64 padded spectrum for free and surface BC).
- * After one solve gps_plan_device_bytes reports *tables + *buffers.  Any
+ * After one solve gps_plan_device_bytes reports *tables + *buffers, or less on
+ * a device without room for what the plane pass alone needs: there the plan
+ * frees that (for good) and keeps to the y, z and y passes.  Any
  * output pointer may be NULL.  Errors: GPS_E_INVALID (n < 2, maxit < 1,
  * unknown bc or precision). */
 gps_status gps_plan_footprint(int nx, int ny, int nz, int bc, int precision, int maxit,

@@ -82,6 +82,29 @@ void dfree(P*& p) {
   p = nullptr;
 }
 
+// Pinned host memory.
+template <typename P>
+void halloc(P** p, size_t bytes) {
+  if (hipHostMalloc(reinterpret_cast<void**>(p), bytes) == hipSuccess) return;
+  (void)hipGetLastError();
+  *p = nullptr;
+  throw NoMem{};
+}
+
+// alloc() as a whole: where one of its allocations fails, undo() frees the others, so
+// that nothing half-built is left for a later call, and *total is what it was.
+template <typename F, typename U>
+void all_or_none(size_t* total, F&& alloc, U&& undo) {
+  const size_t before = *total;
+  try {
+    alloc();
+  } catch (const NoMem&) {
+    undo();
+    *total = before;
+    throw;
+  }
+}
+
 bool factorize(int n, RadixPlan* rp) {
   rp->n = n;
   rp->nstages = 0;
@@ -176,13 +199,12 @@ struct gps_plan {
   double* green64 = nullptr;
   float* green32 = nullptr;
   double* lap64t = nullptr;     // spectral Laplacian table (periodic)
-  // plane pass (FP32, FP64): shapes, and the Green's spectrum in its order; compact:
-  // made without it; no_half: its buffers did not fit, so the y, z, y passes run
+  // plane pass (FP32, FP64): shapes (N = 0: the y, z, y passes run), and the Green's
+  // spectrum in its order; compact: made without it
   PlaneShape shape32{}, shape64{};
   double* plane64 = nullptr;
   float* plane32 = nullptr;
   bool compact = false;
-  bool no_half = false;
   double* pol_lne = nullptr;    // ln eps scratch of gps_polarization_charge (n doubles)
   size_t pol_bytes = 0;
   int* bad_atoms = nullptr;     // pinned: flag of gps_rigid_cavity's atom check
@@ -444,13 +466,6 @@ void alloc_slot(gps_plan* pl, Slot<T>& s, size_t* bytes) {
   if (pl->bc == GPS_BC_PERIODIC) dalloc(&s.s, nb, bytes);
   dalloc(&s.sq64, (size_t)n * sizeof(double), bytes);
   dalloc(&s.work, (size_t)g.nz * g.Ly * g.Kx * sizeof(cplx<T>), bytes);
-  if (pl->shape<T>().N > 0 && !pl->no_half) {
-    try {
-      dalloc(&s.half, (size_t)g.nz * g.ny * g.Kx * sizeof(cplx<T>), bytes);
-    } catch (const NoMem&) {
-      pl->no_half = true;
-    }
-  }
   dalloc(&s.part_init, (size_t)4 * nvg * sizeof(double), bytes);
   dalloc(&s.part_rr, (size_t)nxg * sizeof(double), bytes);
   dalloc(&s.part_delta, (size_t)nzg * sizeof(double), bytes);
@@ -470,34 +485,41 @@ void free_slot(Slot<T>& s) {
   dfree(s.sig64); dfree(s.src64); dfree(s.qk64);
 }
 
+template <typename T> void free_res(gps_plan* pl);
+
+// What the solves of one precision need (all but the plane pass's half spectra).
 template <typename T>
-void ensure_res(gps_plan* pl, bool need_ion, bool need_refine = false) {
-  std::lock_guard<std::mutex> lk(g_plan_mu);
+void grow_res(gps_plan* pl, bool need_ion, bool need_refine) {
   Res<T>& R = pl->res<T>();
   const long long n = pl->npts();
   const int nvg = vec_groups(n);
   const Geom& g = pl->g;
   if (!R.ready) {
-    R.slot() = Slot<T>{};
-    alloc_slot<T>(pl, R.slot(), &R.bytes);
-    if (pl->bc == GPS_BC_PERIODIC) {
-      dalloc(&R.lap64, (size_t)n * sizeof(double), &R.bytes);
-      if (sizeof(T) != sizeof(double))
-        dalloc(&R.work64q, (size_t)g.nz * g.Ly * g.Kx * sizeof(cplx<double>), &R.bytes);
-    }
-    if (hipHostMalloc(reinterpret_cast<void**>(&R.h_state), sizeof(SolveState)) != hipSuccess)
-      throw NoMem{};
-    if (hipHostMalloc(reinterpret_cast<void**>(&R.h_parts), (size_t)4 * nvg * sizeof(double)) !=
-        hipSuccess)
-      throw NoMem{};
+    all_or_none(&R.bytes, [&] {
+      R.slot() = Slot<T>{};
+      alloc_slot<T>(pl, R.slot(), &R.bytes);
+      if (pl->bc == GPS_BC_PERIODIC) {
+        dalloc(&R.lap64, (size_t)n * sizeof(double), &R.bytes);
+        if (sizeof(T) != sizeof(double))
+          dalloc(&R.work64q, (size_t)g.nz * g.Ly * g.Kx * sizeof(cplx<double>), &R.bytes);
+      }
+      halloc(&R.h_state, sizeof(SolveState));
+      halloc(&R.h_parts, (size_t)4 * nvg * sizeof(double));
+    }, [&] { free_res<T>(pl); });
     R.ready = true;
   }
   if (R.hist_cap < pl->opt.maxit + 1) {
-    for (int i = 0; i < R.nslots; ++i) {
-      if (R.slot(i).hist) R.bytes -= (size_t)4 * R.hist_cap * sizeof(double);
-      dfree(R.slot(i).hist);
-      dalloc(&R.slot(i).hist, (size_t)4 * (pl->opt.maxit + 1) * sizeof(double), &R.bytes);
-    }
+    const auto drop = [&] {
+      for (int i = 0; i < R.nslots; ++i) dfree(R.slot(i).hist);
+    };
+    drop_graphs(R);
+    drop();
+    R.bytes -= (size_t)R.nslots * 4 * R.hist_cap * sizeof(double);
+    R.hist_cap = 0;
+    all_or_none(&R.bytes, [&] {
+      for (int i = 0; i < R.nslots; ++i)
+        dalloc(&R.slot(i).hist, (size_t)4 * (pl->opt.maxit + 1) * sizeof(double), &R.bytes);
+    }, drop);
     R.hist_cap = pl->opt.maxit + 1;
   }
   bool changed = false;
@@ -508,11 +530,15 @@ void ensure_res(gps_plan* pl, bool need_ion, bool need_refine = false) {
   if (need_refine && !R.slot().sig64) {
     Slot<T>& s = R.slot();
     const size_t nd = (size_t)n * sizeof(double);
-    dalloc(&s.sig64, nd, &R.bytes);
-    dalloc(&s.src64, nd, &R.bytes);
-    dalloc(&s.qk64, nd, &R.bytes);
-    dalloc(&R.u64, nd, &R.bytes);
-    dalloc(&R.work64r, (size_t)g.nz * g.Ly * g.Kx * sizeof(cplx<double>), &R.bytes);
+    all_or_none(&R.bytes, [&] {
+      dalloc(&s.sig64, nd, &R.bytes);
+      dalloc(&s.src64, nd, &R.bytes);
+      dalloc(&s.qk64, nd, &R.bytes);
+      dalloc(&R.u64, nd, &R.bytes);
+      dalloc(&R.work64r, (size_t)g.nz * g.Ly * g.Kx * sizeof(cplx<double>), &R.bytes);
+    }, [&] {
+      dfree(s.sig64); dfree(s.src64); dfree(s.qk64); dfree(R.u64); dfree(R.work64r);
+    });
     changed = true;
   }
   // the table is captured by value in graphs: rebuild them when it changes
@@ -522,6 +548,57 @@ void ensure_res(gps_plan* pl, bool need_ion, bool need_refine = false) {
     R.slot(i).hist_cap = R.hist_cap;
     R.slot(i).maxit = pl->opt.maxit;
   }
+}
+
+// The plane pass's own memory is optional.  Where the device has no room for a call beside
+// it, the plan gives it back (tables and half spectra) and keeps to the y, z, y passes; the
+// half spectra are allocated last, when a call has all that it needs.
+template <typename T>
+void free_half(Res<T>& R, const Geom& g) {
+  for (int i = 0; i < R.nslots; ++i) {
+    if (!R.slot(i).half) continue;
+    dfree(R.slot(i).half);
+    R.bytes -= (size_t)g.nz * g.ny * g.Kx * sizeof(cplx<T>);
+  }
+}
+
+bool give_back_plane(gps_plan* pl);
+
+template <typename F>
+void with_room(gps_plan* pl, F&& f) {
+  try {
+    f();
+    return;
+  } catch (const NoMem&) {
+    if (!give_back_plane(pl)) throw;
+  }
+  f();
+}
+
+template <typename T>
+void ensure_half(gps_plan* pl) {
+  if (pl->shape<T>().N == 0) return;
+  Res<T>& R = pl->res<T>();
+  const Geom& g = pl->g;
+  bool changed = false;
+  try {
+    for (int i = 0; i < R.nslots; ++i) {
+      if (R.slot(i).half) continue;
+      dalloc(&R.slot(i).half, (size_t)g.nz * g.ny * g.Kx * sizeof(cplx<T>), &R.bytes);
+      changed = true;
+    }
+  } catch (const NoMem&) {
+    give_back_plane(pl);
+    return;
+  }
+  if (changed) drop_graphs(R);           // the slot table changed
+}
+
+template <typename T>
+void ensure_res(gps_plan* pl, bool need_ion, bool need_refine = false) {
+  std::lock_guard<std::mutex> lk(g_plan_mu);
+  with_room(pl, [&] { grow_res<T>(pl, need_ion, need_refine); });
+  ensure_half<T>(pl);
 }
 
 template <typename T>
@@ -536,17 +613,38 @@ void free_res(gps_plan* pl) {
   R = Res<T>{};
 }
 
-void free_sc(gps_plan* pl) {
-  gps_plan::ScRes& S = pl->sc;
-  for (hipGraphExec_t& g : S.graphs) {
+void drop_sc_graphs(gps_plan* pl) {
+  for (hipGraphExec_t& g : pl->sc.graphs) {
     if (g) (void)hipGraphExecDestroy(g);
     g = nullptr;
   }
+}
+
+void free_sc(gps_plan* pl) {
+  gps_plan::ScRes& S = pl->sc;
+  drop_sc_graphs(pl);
   dfree(S.r); dfree(S.v); dfree(S.av); dfree(S.f); dfree(S.lne); dfree(S.eps); dfree(S.phi);
   dfree(S.part_op); dfree(S.part); dfree(S.st);
   if (S.h_st) (void)hipHostFree(S.h_st);
   if (S.h_part) (void)hipHostFree(S.h_part);
   S = gps_plan::ScRes{};
+}
+
+// False if there is nothing to give back.
+bool give_back_plane(gps_plan* pl) {
+  if (!pl->plane32 && !pl->plane64) return false;
+  drop_graphs(pl->r32);
+  drop_graphs(pl->r64);
+  drop_sc_graphs(pl);
+  free_half(pl->r32, pl->g);
+  free_half(pl->r64, pl->g);
+  const size_t n = plane_table_count(pl->g);
+  if (pl->plane32) pl->bytes -= n * sizeof(float);
+  if (pl->plane64) pl->bytes -= n * sizeof(double);
+  dfree(pl->plane32);
+  dfree(pl->plane64);
+  pl->shape32.N = pl->shape64.N = 0;
+  return true;
 }
 
 template <typename T>
@@ -633,14 +731,14 @@ double pass_bytes(const gps_plan* pl, int kind, size_t s) {
     case GPS_K_XFWD: return (5.0 * s + 16.0) * n + rows * g.Kx * c;   // with the fused update
     case GPS_K_YFWD: return (double)g.nz * g.Kx * g.ny * c + wbox * c;
     case GPS_K_ZCONV: {
-      if (s == sizeof(float) && pl->shape32.N > 0 && !pl->no_half)   // plane pass
+      if (s == sizeof(float) && pl->shape32.N > 0)   // plane pass
         return (double)g.nz * g.ny * g.Kx * c + wbox * c +
                (double)(g.Lz / 2 + 1) * g.Ly * g.Kx * s;
       return 2.0 * wbox * c + tab * s;
     }
     case GPS_K_YINV: return wbox * c + (double)g.nz * g.Kx * g.ny * c;
     case GPS_K_XINV: {                                // with the direction update
-      const bool plane = s == sizeof(float) && pl->shape32.N > 0 && !pl->no_half;
+      const bool plane = s == sizeof(float) && pl->shape32.N > 0;
       const double in = plane ? wbox : rows * g.Kx;
       return in * c + (7.0 + periodic) * n * s;
     }
@@ -658,7 +756,7 @@ double pass_bytes(const gps_plan* pl, int kind, size_t s) {
 // 1e-6 differ by 1e-8), and FP64 results are to stay what they are.
 template <typename T>
 bool use_plane(const gps_plan* pl, int refine) {
-  return pl->shape<T>().N > 0 && !pl->no_half && !refine && pl->timing_kind != GPS_K_YFWD &&
+  return pl->shape<T>().N > 0 && !refine && pl->timing_kind != GPS_K_YFWD &&
          pl->timing_kind != GPS_K_YINV;
 }
 
@@ -1139,20 +1237,22 @@ void ensure_sc(gps_plan* pl) {
   const long long n = pl->npts();
   const size_t nd = (size_t)n * sizeof(double);
   const int gv = vec_groups(n), gp = polarization_groups(pl->g);
-  dalloc(&S.r, nd, &S.bytes);
-  dalloc(&S.v, nd, &S.bytes);
-  dalloc(&S.av, nd, &S.bytes);
-  dalloc(&S.f, nd, &S.bytes);
-  dalloc(&S.lne, nd, &S.bytes);
-  dalloc(&S.eps, nd, &S.bytes);
-  dalloc(&S.phi, nd, &S.bytes);
-  dalloc(&S.part_op, (size_t)2 * gp * sizeof(double), &S.bytes);
-  dalloc(&S.part, (size_t)2 * gv * sizeof(double), &S.bytes);
-  dalloc(&S.st, sizeof(ScState), &S.bytes);
-  if (hipHostMalloc(reinterpret_cast<void**>(&S.h_st), sizeof(ScState)) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&S.h_part), (size_t)2 * gv * sizeof(double)) !=
-          hipSuccess)
-    throw NoMem{};
+  with_room(pl, [&] {
+    all_or_none(&S.bytes, [&] {
+      dalloc(&S.r, nd, &S.bytes);
+      dalloc(&S.v, nd, &S.bytes);
+      dalloc(&S.av, nd, &S.bytes);
+      dalloc(&S.f, nd, &S.bytes);
+      dalloc(&S.lne, nd, &S.bytes);
+      dalloc(&S.eps, nd, &S.bytes);
+      dalloc(&S.phi, nd, &S.bytes);
+      dalloc(&S.part_op, (size_t)2 * gp * sizeof(double), &S.bytes);
+      dalloc(&S.part, (size_t)2 * gv * sizeof(double), &S.bytes);
+      dalloc(&S.st, sizeof(ScState), &S.bytes);
+      halloc(&S.h_st, sizeof(ScState));
+      halloc(&S.h_part, (size_t)2 * gv * sizeof(double));
+    }, [&] { free_sc(pl); });
+  });
 }
 
 // The partials that the stop decision of a step sums.
@@ -1322,23 +1422,23 @@ void ensure_batch(gps_plan* pl, int K) {
   std::lock_guard<std::mutex> lk(g_plan_mu);
   Res<T>& R = pl->res<T>();
   if (R.nslots < K) {
-    for (int i = R.nslots; i < K; ++i) {
-      Slot<T>& sl = R.slot(i);
-      sl = Slot<T>{};
-      R.nslots = i + 1;            // free_res frees it even if an allocation below fails
-      alloc_slot<T>(pl, sl, &R.bytes);
-      dalloc(&sl.hist, (size_t)4 * R.hist_cap * sizeof(double), &R.bytes);
-      sl.hist_cap = R.hist_cap;
-      sl.maxit = pl->opt.maxit;
-    }
-    drop_graphs(R);                // the slot table changed
+    drop_graphs(R);                // the slot table changes
+    with_room(pl, [&] {
+      while (R.nslots < K) {
+        Slot<T>& sl = R.slot(R.nslots);
+        sl = Slot<T>{};
+        all_or_none(&R.bytes, [&] {
+          alloc_slot<T>(pl, sl, &R.bytes);
+          dalloc(&sl.hist, (size_t)4 * R.hist_cap * sizeof(double), &R.bytes);
+        }, [&] { free_slot(sl); });
+        sl.hist_cap = R.hist_cap;
+        sl.maxit = pl->opt.maxit;
+        ++R.nslots;
+      }
+    });
+    ensure_half<T>(pl);
   }
-  if (!R.h_states &&
-      hipHostMalloc(reinterpret_cast<void**>(&R.h_states), kArgSlots * sizeof(SolveState)) !=
-          hipSuccess) {
-    R.h_states = nullptr;
-    throw NoMem{};
-  }
+  if (!R.h_states) halloc(&R.h_states, kArgSlots * sizeof(SolveState));
 }
 
 template <typename T>
@@ -1690,7 +1790,6 @@ gps_status gps_plan_release_buffers(gps_plan* pl) {
   dfree(pl->pol_lne);
   pl->pol_bytes = 0;
   free_sc(pl);
-  pl->no_half = false;
   return GPS_OK;
 }
 
@@ -1840,7 +1939,9 @@ gps_status gps_polarization_charge(gps_plan* pl, const double* rho, const double
   try {
     if (!pl->pol_lne) {
       std::lock_guard<std::mutex> lk(g_plan_mu);
-      dalloc(&pl->pol_lne, (size_t)pl->npts() * sizeof(double), &pl->pol_bytes);
+      with_room(pl, [&] {
+        dalloc(&pl->pol_lne, (size_t)pl->npts() * sizeof(double), &pl->pol_bytes);
+      });
     }
     launch_log_field(pl->npts(), eps, pl->pol_lne, pl->stream());
     launch_polarization(pl->g, pl->opt.fd_order / 2, rho, eps, pl->pol_lne, phi, rho_pol,

@@ -1,0 +1,147 @@
+// The plane pass's own memory (reordered Green's tables, half spectra) is optional: whatever
+// a plan can run without it on a device, it runs on that device with it.  For every kind of call,
+// precision and boundary condition, the bytes that a plan made without the pass holds after the
+// call are the limit (and limits up to what the whole plan holds): the whole plan must then
+// succeed too, hold no more than the limit, and give back what it holds.  Below the limit the call
+// fails and may be repeated; nothing leaks.  Exit status 0 = pass.
+#include <cstdio>
+#include <functional>
+#include <vector>
+
+#include "fake_hip.h"
+#include "gps.h"
+
+namespace gps {
+gps_status compact_plan_create(int nx, int ny, int nz, double h, int bc, gps_plan** out);
+gps_status batch_open(gps_plan* pl, int nslots, int check_neutral);
+}  // namespace gps
+
+static int failures = 0, checks = 0;
+#define EXPECT(cond, ...)                                            \
+  do {                                                               \
+    ++checks;                                                        \
+    if (!(cond)) {                                                   \
+      std::fprintf(stderr, "FAILED %s:%d: %s: ", __FILE__, __LINE__, #cond); \
+      std::fprintf(stderr, __VA_ARGS__);                             \
+      std::fprintf(stderr, "\n");                                    \
+      ++failures;                                                    \
+    }                                                                \
+  } while (0)
+
+constexpr int N = 16;
+static std::vector<double> rho(N* N* N, 0.0), eps(N* N* N, 1.0), phi(N* N* N);
+
+using Call = std::function<gps_status(gps_plan*)>;
+struct Kind {
+  const char* name;
+  int precision;
+  bool plane;                  // runs as x, plane, x where the device has room
+  int refine;
+  Call call;
+};
+
+static gps_plan* make(int bc, const Kind& k, bool compact) {
+  gps_plan* p = nullptr;
+  const gps_status st = compact ? gps::compact_plan_create(N, N, N, 0.5, bc, &p)
+                                : gps_plan_create(N, N, N, 0.5, bc, &p);
+  EXPECT(st == GPS_OK, "create %d", st);
+  gps_options o;
+  gps_plan_get_options(p, &o);
+  o.precision = k.precision;
+  o.maxit = 20;
+  o.refine_every = k.refine;
+  EXPECT(gps_plan_set_options(p, &o) == GPS_OK, "options");
+  return p;
+}
+
+static void run(int bc, const Kind& k) {
+  fake::limit = ~size_t(0);
+  gps_plan* p = make(bc, k, true);
+  EXPECT(k.call(p) == GPS_OK, "%s bc %d: compact", k.name, bc);
+  EXPECT(gps_plan_device_bytes(p) == fake::used, "%s bc %d: bytes", k.name, bc);
+  const size_t least = fake::used;
+  gps_plan_destroy(p);
+  EXPECT(fake::used == 0, "%s bc %d: leak", k.name, bc);
+
+  p = make(bc, k, false);
+  fake::launches.clear();
+  EXPECT(k.call(p) == GPS_OK, "%s bc %d: whole", k.name, bc);
+  EXPECT((fake::count("k_plane") > fake::count("k_plane_table")) == k.plane, "%s bc %d: route",
+         k.name, bc);
+  EXPECT(gps_plan_device_bytes(p) == fake::used, "%s bc %d: bytes", k.name, bc);
+  const size_t most = fake::used;
+  EXPECT(most > least, "%s bc %d: whole plan's bytes", k.name, bc);
+  gps_plan_destroy(p);
+
+  for (int i = 0; i <= 8; ++i) {
+    const size_t limit = least + (most - least) * i / 8;
+    fake::limit = ~size_t(0);                    // (the plan's transient may exceed the limit)
+    p = make(bc, k, false);
+    fake::limit = limit;
+    for (int j = 0; j < 2; ++j) {
+      fake::launches.clear();
+      EXPECT(k.call(p) == GPS_OK, "%s bc %d: limit %d of 8, call %d", k.name, bc, i, j);
+      EXPECT(fake::used <= limit, "%s bc %d: %zu bytes above %zu", k.name, bc, fake::used, limit);
+      EXPECT(gps_plan_device_bytes(p) == fake::used, "%s bc %d: bytes", k.name, bc);
+      gps_plan_release_buffers(p);
+    }
+    gps_plan_destroy(p);
+    EXPECT(fake::used == 0, "%s bc %d: leak", k.name, bc);
+  }
+
+  // below what the call needs: an error, twice, then as a fresh plan without the pass
+  for (int i = 1; i <= 40; ++i) {
+    fake::limit = ~size_t(0);
+    p = make(bc, k, false);
+    gps_plan* bare = make(bc, k, true);
+    const size_t tables = gps_plan_device_bytes(bare);
+    gps_plan_destroy(bare);
+    fake::limit = tables + (least - tables) * i / 41;
+    for (int j = 0; j < 2; ++j)
+      EXPECT(k.call(p) == GPS_E_NOMEM, "%s bc %d: %d of 41, call %d", k.name, bc, i, j);
+    EXPECT(gps_plan_device_bytes(p) == fake::used, "%s bc %d: bytes after an error", k.name, bc);
+    fake::limit = ~size_t(0);
+    EXPECT(k.call(p) == GPS_OK, "%s bc %d: %d of 41, then room", k.name, bc, i);
+    EXPECT(fake::used == least, "%s bc %d: %d of 41: %zu bytes, not %zu", k.name, bc, i, fake::used,
+           least);
+    gps_plan_destroy(p);
+    EXPECT(fake::used == 0, "%s bc %d: leak", k.name, bc);
+  }
+}
+
+int main() {
+  const Call solve = [](gps_plan* p) {
+    return gps_solve_generalized(p, rho.data(), eps.data(), phi.data(), 1e-6);
+  };
+  const Call vacuum = [](gps_plan* p) { return gps_solve_vacuum(p, rho.data(), phi.data()); };
+  const Call sc = [](gps_plan* p) {
+    return gps_solve_sc(p, rho.data(), eps.data(), phi.data(), 1e-6, GPS_METHOD_SC, 0.6);
+  };
+  const Call batch = [](gps_plan* p) { return gps::batch_open(p, 3, 0); };
+  // a solve and then the polarization charge: the scratch field comes last
+  const Call both = [](gps_plan* p) {
+    const gps_status st = gps_solve_generalized(p, rho.data(), eps.data(), phi.data(), 1e-6);
+    return st != GPS_OK ? st
+                        : gps_polarization_charge(p, rho.data(), eps.data(), phi.data(), phi.data());
+  };
+  const Kind kinds[] = {
+      {"solve mixed", GPS_PREC_MIXED, true, 0, solve},
+      {"solve fp64", GPS_PREC_FP64, false, 0, solve},
+      {"refined mixed", GPS_PREC_MIXED, false, 5, solve},
+      {"vacuum mixed", GPS_PREC_MIXED, true, 0, vacuum},
+      {"vacuum fp64", GPS_PREC_FP64, true, 0, vacuum},
+      {"sc mixed", GPS_PREC_MIXED, true, 0, sc},
+      {"sc fp64", GPS_PREC_FP64, true, 0, sc},
+      {"batch mixed", GPS_PREC_MIXED, true, 0, batch},
+      {"batch fp64", GPS_PREC_FP64, false, 0, batch},
+      {"solve and polarization mixed", GPS_PREC_MIXED, true, 0, both},
+  };
+  for (int bc : {GPS_BC_FREE, GPS_BC_SURFACE, GPS_BC_PERIODIC, GPS_BC_WIRE})
+    for (const Kind& k : kinds) {
+      const bool periodic = bc == GPS_BC_PERIODIC;
+      if (periodic && (k.refine > 0 || std::strncmp(k.name, "sc", 2) == 0)) continue;
+      run(bc, k);
+    }
+  std::printf("plane memory: %d checks, %d failures\n", checks, failures);
+  return failures == 0 ? 0 : 1;
+}
