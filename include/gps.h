@@ -157,7 +157,7 @@ size_t gps_plan_device_bytes(const gps_plan *plan);
 /* Device bytes of a plan for an nx x ny x nz grid with boundary condition bc:
  * *tables, held from gps_plan_create to gps_plan_destroy (twiddles, Green's
  * spectrum, and its copy in the plane pass's order for the grids that have one);
- * *buffers, the per-solve buffers that one solve in `precision`
+ * *buffers, the per-solve buffers that one PCG solve in `precision`
  * with iteration cap maxit allocates (nonlinear_pb != 0: a nonlinear
  * Poisson-Boltzmann solve, which adds the ionic-charge field; refine != 0:
  * true-residual refinement or warm start on, which adds their FP64 buffers) and
@@ -208,6 +208,10 @@ gps_status gps_solve_pb(gps_plan *plan, const double *rho, const double *eps,
  * sqrt(eps) scaling).  Arithmetic in the plan's bulk precision.  f, u:
  * device double[nz][ny][nx]; f is read, u written (they may not alias).
  * Periodic: the k = 0 component of f is dropped (u has zero mean).
+ * On grids with the plane pass the first FP64 call (as that of gps_solve_sc)
+ * allocates the pass's half spectrum, nz*ny*(Lx/2 + 1) complex values (Lx the
+ * FFT length along x), beside the buffers of a solve; the plan keeps it until
+ * gps_plan_release_buffers or gps_plan_destroy.
  * Errors: GPS_E_INVALID (null pointer), GPS_E_NOMEM, GPS_E_DEVICE. */
 gps_status gps_solve_vacuum(gps_plan *plan, const double *f, double *u);
 
@@ -380,7 +384,7 @@ const char *gps_status_string(int status);
  * room, idle plans release their buffers (gps_plan_release_buffers) and then
  * are destroyed, least recently used first in both steps.  Otherwise the request waits until
  * a running solve finishes.  A request that alone exceeds the budget runs on a plan without
- * the plane pass where that fits.  Requests are taken in arrival order, except that
+ * the plane pass where that fits, as every FP64 request does (none uses it).  Requests are taken in arrival order, except that
  * a waiting request among the next 16 whose plan is resident and idle may go
  * ahead of older ones that need a new plan.  No request is passed over more
  * than 8 times.

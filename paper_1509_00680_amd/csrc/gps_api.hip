@@ -552,7 +552,8 @@ void grow_res(gps_plan* pl, bool need_ion, bool need_refine) {
 
 // The plane pass's own memory is optional.  Where the device has no room for a call beside
 // it, the plan gives it back (tables and half spectra) and keeps to the y, z, y passes; the
-// half spectra are allocated last, when a call has all that it needs.
+// half spectra are allocated last, when a call has all that it needs.  Every FP32 call
+// has one; in FP64 only the vacuum solve and SC/PSD take the pass, and allocate it.
 template <typename T>
 void free_half(Res<T>& R, const Geom& g) {
   for (int i = 0; i < R.nslots; ++i) {
@@ -598,7 +599,7 @@ template <typename T>
 void ensure_res(gps_plan* pl, bool need_ion, bool need_refine = false) {
   std::lock_guard<std::mutex> lk(g_plan_mu);
   with_room(pl, [&] { grow_res<T>(pl, need_ion, need_refine); });
-  ensure_half<T>(pl);
+  if (sizeof(T) == sizeof(float)) ensure_half<T>(pl);
 }
 
 template <typename T>
@@ -755,8 +756,8 @@ double pass_bytes(const gps_plan* pl, int kind, size_t s) {
 // multiplies a change of rounding by up to 1e8 (solutions of 32^3 to 64^3 at
 // 1e-6 differ by 1e-8), and FP64 results are to stay what they are.
 template <typename T>
-bool use_plane(const gps_plan* pl, int refine) {
-  return pl->shape<T>().N > 0 && !refine && pl->timing_kind != GPS_K_YFWD &&
+bool use_plane(gps_plan* pl, int refine) {
+  return pl->shape<T>().N > 0 && pl->res<T>().slot().half && !refine && pl->timing_kind != GPS_K_YFWD &&
          pl->timing_kind != GPS_K_YINV;
 }
 
@@ -930,6 +931,10 @@ void enqueue_vacuum(gps_plan* pl, const double* f, double* u, hipStream_t s,
 template <typename T>
 void vacuum_apply(gps_plan* pl, const double* f, double* u) {
   ensure_res<T>(pl, false);
+  {
+    std::lock_guard<std::mutex> lk(g_plan_mu);
+    ensure_half<T>(pl);
+  }
   enqueue_vacuum<T>(pl, f, u, pl->stream());
   ck(hipGetLastError());
   ck(hipStreamSynchronize(pl->stream()));
@@ -1232,12 +1237,11 @@ template <typename T>
 void ensure_sc(gps_plan* pl) {
   ensure_res<T>(pl, false);
   gps_plan::ScRes& S = pl->sc;
-  if (S.st) return;
   std::lock_guard<std::mutex> lk(g_plan_mu);
   const long long n = pl->npts();
   const size_t nd = (size_t)n * sizeof(double);
   const int gv = vec_groups(n), gp = polarization_groups(pl->g);
-  with_room(pl, [&] {
+  if (!S.st) with_room(pl, [&] {
     all_or_none(&S.bytes, [&] {
       dalloc(&S.r, nd, &S.bytes);
       dalloc(&S.v, nd, &S.bytes);
@@ -1253,6 +1257,7 @@ void ensure_sc(gps_plan* pl) {
       halloc(&S.h_part, (size_t)2 * gv * sizeof(double));
     }, [&] { free_sc(pl); });
   });
+  ensure_half<T>(pl);
 }
 
 // The partials that the stop decision of a step sums.
@@ -1436,7 +1441,7 @@ void ensure_batch(gps_plan* pl, int K) {
         ++R.nslots;
       }
     });
-    ensure_half<T>(pl);
+    if (sizeof(T) == sizeof(float)) ensure_half<T>(pl);
   }
   if (!R.h_states) halloc(&R.h_states, kArgSlots * sizeof(SolveState));
 }
@@ -1822,7 +1827,7 @@ static gps_status plan_footprint(int nx, int ny, int nz, int bc, int precision, 
     const bool has64 = plane_shape(g, sizeof(double)).N > 0;
     const size_t np = (Lz / 2 + 1) * Ly * Kx;
     tb += (has32 ? np * sizeof(float) : 0) + (has64 ? np * sizeof(double) : 0);
-    if (s == sizeof(float) ? has32 : has64) half = (size_t)nz * ny * Kx * 2 * s;
+    if (s == sizeof(float) && has32) half = (size_t)nz * ny * Kx * 2 * s;
   }
   size_t b = 5 * n * s + (pz ? n * s : 0) + n * sizeof(double);                     // vectors, sq64
   b += wbox * 2 * s + half;                                                   // work buffers

@@ -33,9 +33,10 @@ struct BatchSlot {
   double rr0;         // ||r_0||^2
 };
 
-// A plan without the plane pass's table and buffers, and its footprint: as
-// gps_plan_create and gps_plan_footprint, for a memory budget that the whole
-// plan would exceed.  The same results to rounding.
+// A plan without the plane pass's tables and buffers, and its footprint: as
+// gps_plan_create and gps_plan_footprint, for FP64 PCG solves, which do not take
+// the pass (the same bits), and for a memory budget that the whole plan would
+// exceed (the same results to rounding).
 gps_status compact_plan_create(int nx, int ny, int nz, double h, int bc, gps_plan** out);
 gps_status compact_plan_footprint(int nx, int ny, int nz, int bc, int precision, int maxit,
                                   int nonlinear_pb, int refine, size_t* tables, size_t* buffers,

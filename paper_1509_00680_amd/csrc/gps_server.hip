@@ -37,7 +37,8 @@ constexpr int kServeChunk = 8;
 struct PlanKey {
   int nx, ny, nz, bc;
   double h;
-  bool compact;            // without the plane pass (the whole plan exceeds the budget)
+  bool compact;            // without the plane pass: FP64 solves (none takes it), and requests
+                           // whose whole plan exceeds the budget
   bool operator==(const PlanKey& o) const {
     return nx == o.nx && ny == o.ny && nz == o.nz && bc == o.bc && h == o.h &&
            compact == o.compact;
@@ -588,28 +589,30 @@ gps_status gps_server_submit(gps_server* S, const gps_request* q, long long* tic
   }
   const int nonlinear = R->has_ions && !R->ions.linear;
   R->tracked = q->eps_key != 0 && q->bc != GPS_BC_PERIODIC && !nonlinear;
-  if (gps_plan_footprint(q->nx, q->ny, q->nz, q->bc, S->opt.precision, S->opt.maxit, nonlinear,
-                         R->tracked ? 1 : 0, &R->tables, &R->buffers, &R->transient) != GPS_OK) {
-    delete R;
-    return GPS_E_INVALID;
-  }
   R->neutral = q->bc == GPS_BC_PERIODIC && !R->has_ions;
   R->batchable = S->opt.batch_slots > 1 && !nonlinear && !R->tracked &&
                  (long long)q->nx * q->ny * q->nz <= kBatchMaxPoints;
-  if (R->batchable) R->buffers *= (size_t)S->opt.batch_slots;   // a plan of batch_slots slots
+  const auto footprint = [&](bool compact) {
+    R->key.compact = compact;
+    const gps_status st =
+        (compact ? gps::compact_plan_footprint : gps_plan_footprint)(
+            q->nx, q->ny, q->nz, q->bc, S->opt.precision, S->opt.maxit, nonlinear,
+            R->tracked ? 1 : 0, &R->tables, &R->buffers, &R->transient);
+    if (R->batchable) R->buffers *= (size_t)S->opt.batch_slots;   // a plan of batch_slots slots
+    return st;
+  };
   const auto exceeds = [&] {
     return S->opt.budget_bytes && R->tables + R->buffers + R->transient > S->opt.budget_bytes;
   };
-  if (exceeds()) {                       // alone over the budget: without the plane pass
-    R->key.compact = true;
-    gps::compact_plan_footprint(q->nx, q->ny, q->nz, q->bc, S->opt.precision, S->opt.maxit,
-                                nonlinear, R->tracked ? 1 : 0, &R->tables, &R->buffers,
-                                &R->transient);
-    if (R->batchable) R->buffers *= (size_t)S->opt.batch_slots;
-    if (exceeds()) {
-      delete R;
-      return GPS_E_NOMEM;
-    }
+  const bool fp64 = S->opt.precision == GPS_PREC_FP64;
+  if (footprint(fp64) != GPS_OK) {
+    delete R;
+    return GPS_E_INVALID;
+  }
+  if (exceeds() && !fp64) footprint(true);   // alone over the budget: without the plane pass
+  if (exceeds()) {
+    delete R;
+    return GPS_E_NOMEM;
   }
   std::lock_guard<std::mutex> lk(S->mu);
   R->ticket = S->next_ticket++;

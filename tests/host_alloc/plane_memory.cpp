@@ -3,7 +3,9 @@
 // precision and boundary condition, the bytes that a plan made without the pass holds after the
 // call are the limit (and limits up to what the whole plan holds): the whole plan must then
 // succeed too, hold no more than the limit, and give back what it holds.  Below the limit the call
-// fails and may be repeated; nothing leaks.  Exit status 0 = pass.
+// fails and may be repeated; nothing leaks.  Calls that never take the pass (FP64 PCG) allocate
+// nothing for it beyond the plan's tables, and a server of FP64 solves nothing at all.  Exit
+// status 0 = pass.
 #include <cstdio>
 #include <functional>
 #include <vector>
@@ -13,6 +15,9 @@
 
 namespace gps {
 gps_status compact_plan_create(int nx, int ny, int nz, double h, int bc, gps_plan** out);
+gps_status compact_plan_footprint(int nx, int ny, int nz, int bc, int precision, int maxit,
+                                  int nonlinear_pb, int refine, size_t* tables, size_t* buffers,
+                                  size_t* transient);
 gps_status batch_open(gps_plan* pl, int nslots, int check_neutral);
 }  // namespace gps
 
@@ -71,6 +76,17 @@ static void run(int bc, const Kind& k) {
   EXPECT(gps_plan_device_bytes(p) == fake::used, "%s bc %d: bytes", k.name, bc);
   const size_t most = fake::used;
   EXPECT(most > least, "%s bc %d: whole plan's bytes", k.name, bc);
+  if (k.precision == GPS_PREC_FP64 && !k.plane) {
+    gps_plan* bare = nullptr;
+    gps_plan* full = nullptr;
+    gps::compact_plan_create(N, N, N, 0.5, bc, &bare);
+    gps_plan_create(N, N, N, 0.5, bc, &full);
+    const size_t tables = gps_plan_device_bytes(full) - gps_plan_device_bytes(bare);
+    gps_plan_destroy(bare);
+    gps_plan_destroy(full);
+    EXPECT(most - least == tables, "%s bc %d: %zu bytes beside the tables", k.name, bc,
+           most - least - tables);
+  }
   gps_plan_destroy(p);
 
   for (int i = 0; i <= 8; ++i) {
@@ -109,6 +125,53 @@ static void run(int bc, const Kind& k) {
   }
 }
 
+// An FP64 server whose budget holds two plans without the pass keeps both.
+static void serve_fp64(int bc) {
+  fake::limit = ~size_t(0);
+  const int sizes[2] = {16, 18}, slots = 2;
+  size_t budget = 0, transient = 0;
+  for (int n : sizes) {
+    size_t t = 0, b = 0, tr = 0;
+    gps::compact_plan_footprint(n, n, n, bc, GPS_PREC_FP64, 20, 0, 0, &t, &b, &tr);
+    budget += t + slots * b;
+    transient = tr;                  // the second plan's: while it is made the first is resident
+  }
+  budget += transient;
+  gps_server_options o{};
+  o.budget_bytes = budget;
+  o.max_active = 1;
+  o.precision = GPS_PREC_FP64;
+  o.fd_order = 16;
+  o.maxit = 20;
+  o.batch_slots = slots;
+  gps_server* srv = nullptr;
+  EXPECT(gps_server_create(&o, &srv) == GPS_OK, "server");
+  std::vector<double> f(18 * 18 * 18, 0.0), e(f.size(), 1.0), u(f.size());
+  for (int i = 0; i < 4; ++i) {
+    const int n = sizes[i % 2];
+    gps_request q{};
+    q.nx = q.ny = q.nz = n;
+    q.h = 0.5;
+    q.bc = bc;
+    q.rho = f.data();
+    q.eps = e.data();
+    q.phi = u.data();
+    q.tol = 1e-6;
+    long long t = 0;
+    gps_result res{};
+    EXPECT(gps_server_submit(srv, &q, &t) == GPS_OK, "submit bc %d, %d", bc, i);
+    EXPECT(gps_server_wait(srv, t, &res) == GPS_OK && res.status == GPS_OK, "bc %d, %d", bc, i);
+    EXPECT(res.plan_reused == (i >= 2), "bc %d: request %d made a plan again", bc, i);
+  }
+  gps_server_stats st{};
+  gps_server_get_stats(srv, &st);
+  EXPECT(st.plans_evicted == 0 && st.buffers_released == 0, "bc %d: %d evicted, %d released", bc,
+         st.plans_evicted, st.buffers_released);
+  EXPECT(st.bytes_peak <= budget, "bc %d: peak", bc);
+  gps_server_destroy(srv);
+  EXPECT(fake::used == 0, "bc %d: leak", bc);
+}
+
 int main() {
   const Call solve = [](gps_plan* p) {
     return gps_solve_generalized(p, rho.data(), eps.data(), phi.data(), 1e-6);
@@ -142,6 +205,13 @@ int main() {
       if (periodic && (k.refine > 0 || std::strncmp(k.name, "sc", 2) == 0)) continue;
       run(bc, k);
     }
+  for (int bc : {GPS_BC_FREE, GPS_BC_SURFACE, GPS_BC_PERIODIC, GPS_BC_WIRE}) {
+    serve_fp64(bc);
+    size_t t0 = 0, b0 = 0, t1 = 0, b1 = 0;
+    gps_plan_footprint(N, N, N, bc, GPS_PREC_FP64, 20, 0, 0, &t0, &b0, nullptr);
+    gps::compact_plan_footprint(N, N, N, bc, GPS_PREC_FP64, 20, 0, 0, &t1, &b1, nullptr);
+    EXPECT(b0 == b1 && t0 > t1, "bc %d: FP64 footprint", bc);
+  }
   std::printf("plane memory: %d checks, %d failures\n", checks, failures);
   return failures == 0 ? 0 : 1;
 }
