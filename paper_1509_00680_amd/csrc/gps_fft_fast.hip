@@ -34,34 +34,13 @@ GPS_TUNED_LENGTH(20, 16)
 GPS_TUNED_LENGTH(24, 16)
 #undef GPS_TUNED_LENGTH
 
-// The x passes of lengths 32, 48 and 64 on grids of up to 4096 rows: 4 row
-// pairs.  There the latency of a work-group counts, not their number: 32^3
-// (FP32) 1038 -> 1008 us a solve (3 pairs: the same; 8: slower).  A box of
-// 160 x 160 x 48 points (25,600 rows, 3200 work-groups that each re-sum as
-// many partials) was 2 % slower at 4, so the line is drawn at the largest
-// row count measured to gain.  FP32 only: the order of the partial sums is
-// part of an FP64 solve's rounding, which PCG amplifies (Roots2Pi).
-constexpr int kFewRows = 4096;
-static const LengthPasses g_few_rows[] = {TwoLevel<8, 4, 4, true>::passes(),
-                                          TwoLevel<8, 6, 4, true>::passes(),
-                                          TwoLevel<8, 8, 4, true>::passes()};
-
-template <typename T> const LengthPasses& x_passes(int L, int nrows) {
-  if (sizeof(T) == sizeof(float) && nrows <= kFewRows)
-    for (const LengthPasses& e : g_few_rows)
-      if (e.L == L) return e;
-  return g_passes[L];
-}
-
 bool fast_length(int L) { return L >= 1 && L <= kMaxFastLen && g_passes[L].L == L; }
 
 // Partials of the solve-mode x passes: one per work-group.
-template <typename T> int fast_xpass_parts(int L, int nrows) {
-  const int P = x_passes<T>(L, nrows).P;
+int fast_xpass_parts(int L, int nrows) {
+  const int P = g_passes[L].P;
   return ((nrows + 1) / 2 + P - 1) / P;
 }
-template int fast_xpass_parts<float>(int, int);
-template int fast_xpass_parts<double>(int, int);
 
 // z pass (solve mode): one partial per wavefront
 template <typename T> int fast_strided_parts(const SParams<T>& p) {
@@ -83,16 +62,16 @@ template <> bool fast_strided<double>(int mode, const SParams<double>& p, hipStr
   return true;
 }
 template <> bool fast_xfwd<float>(int mode, const XParams<float>& p, hipStream_t s) {
-  return fast_length(p.g.Lx) && x_passes<float>(p.g.Lx, p.nrows).xfwd32(mode, p, s);
+  return fast_length(p.g.Lx) && g_passes[p.g.Lx].xfwd32(mode, p, s);
 }
 template <> bool fast_xfwd<double>(int mode, const XParams<double>& p, hipStream_t s) {
-  return fast_length(p.g.Lx) && x_passes<double>(p.g.Lx, p.nrows).xfwd64(mode, p, s);
+  return fast_length(p.g.Lx) && g_passes[p.g.Lx].xfwd64(mode, p, s);
 }
 template <> bool fast_xinv<float>(int mode, const XParams<float>& p, hipStream_t s) {
-  return fast_length(p.g.Lx) && x_passes<float>(p.g.Lx, p.nrows).xinv32(mode, p, s);
+  return fast_length(p.g.Lx) && g_passes[p.g.Lx].xinv32(mode, p, s);
 }
 template <> bool fast_xinv<double>(int mode, const XParams<double>& p, hipStream_t s) {
-  return fast_length(p.g.Lx) && x_passes<double>(p.g.Lx, p.nrows).xinv64(mode, p, s);
+  return fast_length(p.g.Lx) && g_passes[p.g.Lx].xinv64(mode, p, s);
 }
 
 }  // namespace gps

@@ -184,7 +184,7 @@ struct LengthPasses {
 constexpr int kMaxFastLen = 448;     // longest length with two-level passes
 bool add_length_passes(const LengthPasses& e);
 bool fast_length(int L);
-template <typename T> int fast_xpass_parts(int L, int nrows);
+int fast_xpass_parts(int L, int nrows);
 template <typename T> int fast_strided_parts(const SParams<T>& p);   // z pass (solve mode)
 template <typename T> bool fast_strided(int mode, const SParams<T>& p, hipStream_t s);
 template <typename T> bool fast_xfwd(int mode, const XParams<T>& p, hipStream_t s);
