@@ -208,7 +208,8 @@ gps_status gps_solve_pb(gps_plan *plan, const double *rho, const double *eps,
  * sqrt(eps) scaling).  Arithmetic in the plan's bulk precision.  f, u:
  * device double[nz][ny][nx]; f is read, u written (they may not alias).
  * Periodic: the k = 0 component of f is dropped (u has zero mean).
- * On grids with the plane pass the first FP64 call (as that of gps_solve_sc)
+ * On grids with the plane pass whose PCG solves do not take it (every FP64 one,
+ * and FP32 ones on large grids) the first call, as that of gps_solve_sc,
  * allocates the pass's half spectrum, nz*ny*(Lx/2 + 1) complex values (Lx the
  * FFT length along x), beside the buffers of a solve; the plan keeps it until
  * gps_plan_release_buffers or gps_plan_destroy.

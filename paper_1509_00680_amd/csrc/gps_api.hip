@@ -552,8 +552,8 @@ void grow_res(gps_plan* pl, bool need_ion, bool need_refine) {
 
 // The plane pass's own memory is optional.  Where the device has no room for a call beside
 // it, the plan gives it back (tables and half spectra) and keeps to the y, z, y passes; the
-// half spectra are allocated last, when a call has all that it needs.  Every FP32 call
-// has one; in FP64 only the vacuum solve and SC/PSD take the pass, and allocate it.
+// half spectra are allocated last, when a call has all that it needs: by every call
+// where PCG solves take the pass, else by the vacuum solve and SC/PSD alone.
 template <typename T>
 void free_half(Res<T>& R, const Geom& g) {
   for (int i = 0; i < R.nslots; ++i) {
@@ -599,7 +599,7 @@ template <typename T>
 void ensure_res(gps_plan* pl, bool need_ion, bool need_refine = false) {
   std::lock_guard<std::mutex> lk(g_plan_mu);
   with_room(pl, [&] { grow_res<T>(pl, need_ion, need_refine); });
-  if (sizeof(T) == sizeof(float)) ensure_half<T>(pl);
+  if (pl->shape<T>().solve) ensure_half<T>(pl);
 }
 
 template <typename T>
@@ -732,14 +732,14 @@ double pass_bytes(const gps_plan* pl, int kind, size_t s) {
     case GPS_K_XFWD: return (5.0 * s + 16.0) * n + rows * g.Kx * c;   // with the fused update
     case GPS_K_YFWD: return (double)g.nz * g.Kx * g.ny * c + wbox * c;
     case GPS_K_ZCONV: {
-      if (s == sizeof(float) && pl->shape32.N > 0)   // plane pass
+      if (s == sizeof(float) && pl->shape32.N > 0 && pl->shape32.solve)   // plane pass
         return (double)g.nz * g.ny * g.Kx * c + wbox * c +
                (double)(g.Lz / 2 + 1) * g.Ly * g.Kx * s;
       return 2.0 * wbox * c + tab * s;
     }
     case GPS_K_YINV: return wbox * c + (double)g.nz * g.Kx * g.ny * c;
     case GPS_K_XINV: {                                // with the direction update
-      const bool plane = s == sizeof(float) && pl->shape32.N > 0;
+      const bool plane = s == sizeof(float) && pl->shape32.N > 0 && pl->shape32.solve;
       const double in = plane ? wbox : rows * g.Kx;
       return in * c + (7.0 + periodic) * n * s;
     }
@@ -752,9 +752,10 @@ double pass_bytes(const gps_plan* pl, int kind, size_t s) {
 // ---------------------------------------------------------------------------
 // Whether the vacuum solver of this plan runs as x, plane, x.  A solve with
 // refinement keeps the y, z, y passes (its FP64 sources live in their x
-// passes), and so does a timed y pass.  So do all FP64 PCG solves: PCG
-// multiplies a change of rounding by up to 1e8 (solutions of 32^3 to 64^3 at
-// 1e-6 differ by 1e-8), and FP64 results are to stay what they are.
+// passes), and so does a timed y pass.  So do PCG solves where the shape says
+// so (PlaneShape::solve), all FP64 ones among them: PCG multiplies a change of
+// rounding by up to 1e8 (solutions of 32^3 to 64^3 at 1e-6 differ by 1e-8), and
+// FP64 results are to stay what they are.
 template <typename T>
 bool use_plane(gps_plan* pl, int refine) {
   return pl->shape<T>().N > 0 && pl->res<T>().slot().half && !refine && pl->timing_kind != GPS_K_YFWD &&
@@ -788,7 +789,7 @@ void enqueue_iteration(gps_plan* pl, const SlotTable<T>& tab, const Batch& b, in
   check_parts(xp.n_pap_parts, part_caps(g).x);
   xp.periodic_mean = periodic;
   if constexpr (sizeof(T) == sizeof(float)) {
-    if (use_plane<T>(pl, refine)) {
+    if (pl->shape<T>().solve && use_plane<T>(pl, refine)) {
       xp.sh = pl->shape<T>();
       xp.dec.n_rr = xp.n_pap_parts;
       xp.dec.n_delta = plane_groups(g.Kx);
@@ -1441,7 +1442,7 @@ void ensure_batch(gps_plan* pl, int K) {
         ++R.nslots;
       }
     });
-    if (sizeof(T) == sizeof(float)) ensure_half<T>(pl);
+    if (pl->shape<T>().solve) ensure_half<T>(pl);
   }
   if (!R.h_states) halloc(&R.h_states, kArgSlots * sizeof(SolveState));
 }
@@ -1823,11 +1824,12 @@ static gps_status plan_footprint(int nx, int ny, int nz, int bc, int precision, 
   size_t half = 0;                                                            // plane pass
   if (!compact && Lx <= (size_t)kMaxLen && Ly <= (size_t)kMaxLen && Lz <= (size_t)kMaxLen) {
     const Geom g = make_geom(nx, ny, nz, 1.0, bc);
-    const bool has32 = plane_shape(g, sizeof(float)).N > 0;
+    const PlaneShape sh32 = plane_shape(g, sizeof(float));
+    const bool has32 = sh32.N > 0;
     const bool has64 = plane_shape(g, sizeof(double)).N > 0;
     const size_t np = (Lz / 2 + 1) * Ly * Kx;
     tb += (has32 ? np * sizeof(float) : 0) + (has64 ? np * sizeof(double) : 0);
-    if (s == sizeof(float) && has32) half = (size_t)nz * ny * Kx * 2 * s;
+    if (s == sizeof(float) && has32 && sh32.solve) half = (size_t)nz * ny * Kx * 2 * s;
   }
   size_t b = 5 * n * s + (pz ? n * s : 0) + n * sizeof(double);                     // vectors, sq64
   b += wbox * 2 * s + half;                                                   // work buffers

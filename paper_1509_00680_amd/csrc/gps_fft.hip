@@ -537,15 +537,33 @@ static bool plane_split(int n, bool along_z, bool even, int* a, int* b) {
 // Dynamic LDS of the plane kernels: a CU's 160 KB less their static words.
 constexpr int kPlaneLds = 160 * 1024 - 512;
 
-// The plane pass runs where its tile fits one work-group's LDS (up to 96^3 free or
-// 128^3 periodic in FP32, 64^3 or 112^3 in FP64) and where the work-groups are
-// many enough for their size: lds <= 1100 per group.  Solves and vacuum solves of 70
-// random grids of 18 to 120 points: 1.01 to 1.20 x the y, z, y passes on this side
-// of the line (two FP64 grids at 0.996), 0.97 x beyond it (FP64, 105 x 108 x 70
-// periodic: 72 groups of 96 KB; 96^3 surface: 98 groups of 150 KB).
+// The plane pass runs where its tile fits one work-group's LDS (FP32: cubes up to
+// 98^3 free and wire, 180^3 periodic; FP64: 63^3 free, 98^3 wire, 128^3 periodic), where the
+// work-groups are many enough for their size, and on grids small enough that
+// its launches and transposes count.  Measured against the y, z, y passes, x the
+// time of the latter over the former:
+//   lds <= 1100 per group    70 random grids of 18 to 120 points 1.01 to 1.20 on this
+//                            side (two FP64 grids at 0.996), 0.97 beyond it (FP64, 105 x 108
+//                            x 70 periodic: 72 groups of 96 KB; 96^3 surface: 98 of 150 KB)
+//   n <= 5e6                 vacuum solves (FP32 and FP64) of 69 grids of 0.3 to 4.8 million
+//                            points: 1.02 to 1.23; of four beyond: 0.98 to 1.02
+// PCG solves (FP32 alone, see use_plane in gps_api.hip) carry the direction update
+// in the x inverse, which beside the plane pass takes more registers and, on a large grid, more
+// of the iteration than the transposes:
+//   n <= 1.5e6               45 grids: 1.01 to 1.24
+//   n <= 3.5e6               where a thread of the x inverse holds at most 209 values (its
+//                            kernel 254 VGPRs, two wavefronts per SIMD): 53 grids, 0.99 to 1.23,
+//                            mean 1.07; where it holds more (periodic x lengths 81, 100, 108,
+//                            120, 144, 168, 180, 196): eight grids, 0.90 to 0.98
+//   beyond                   16 grids of 3.6 to 7.5 million points: 0.85 to 1.03, mean 0.96
+constexpr long long kPlanePoints = 5000000, kPlaneSolvePoints = 3500000, kPlaneFewPoints = 1500000;
+constexpr int kPlaneSolveValues = 209;
+
 PlaneShape plane_shape(const Geom& g, size_t elem) {
   PlaneShape none{};
-  if (!fast_length(g.Lx) || g.Lx > kPlaneMaxLx || g.Ly % kPlaneParts) return none;
+  const long long n = (long long)g.nx * g.ny * g.nz;
+  if (!fast_length(g.Lx) || g.Lx > kPlaneMaxLx || g.Ly % kPlaneParts || n > kPlanePoints)
+    return none;
   PlaneShape s{};
   s.nz = g.nz;
   s.ny = g.ny;
@@ -559,6 +577,9 @@ PlaneShape plane_shape(const Geom& g, size_t elem) {
   s.PY = s.N | 1;                     // odd: the y steps' lanes run over z
   s.lds = ((size_t)s.PY * s.Lz + s.Lz + 2 * s.N) * 2 * elem;
   if (s.lds > (size_t)kPlaneLds || s.lds > 1100 * (size_t)plane_groups(g.Kx)) return none;
+  const int periodic = g.periodic_x && g.periodic_y && g.periodic_z;
+  s.solve = elem == sizeof(float) && n <= kPlaneSolvePoints &&
+            (n <= kPlaneFewPoints || fast_xinv_values(g.Lx, g.nx, periodic) <= kPlaneSolveValues);
   // threads: the count whose four kinds of steps take the fewest rounds, weighed
   // by their lengths and about 8 more for a step's fixed work
   const int jobs[4] = {s.nz * s.A2, s.nz * s.A1, s.N * s.C2, s.N * s.C1};

@@ -42,6 +42,16 @@ int fast_xpass_parts(int L, int nrows) {
   return ((nrows + 1) / 2 + P - 1) / P;
 }
 
+// As the arrays of k_fxinv: KP pairs of rows from both parities, EOUT points with
+// their five fields (six with the mean term), ETW twiddles, the shares of delta (and mu).
+int fast_xinv_values(int L, int lout, int periodic_mean) {
+  const LengthPasses& e = g_passes[L];
+  const int NT = xthreads(e.L1, e.L2, e.P), KS = NT / e.P;
+  const int KP = (L / 2 + 1 + KS - 1) / KS, EOUT = (2 * e.P * lout + NT - 1) / NT;
+  const int shares = (NT == 64 ? 16 : 8) * (periodic_mean ? 2 : 1);
+  return 8 * KP + (periodic_mean ? 6 : 5) * EOUT + 2 * ((L + NT - 1) / NT) + 2 * shares;
+}
+
 // z pass (solve mode): one partial per wavefront
 template <typename T> int fast_strided_parts(const SParams<T>& p) {
   const LengthPasses& e = g_passes[p.L];

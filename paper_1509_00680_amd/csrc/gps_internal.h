@@ -158,6 +158,7 @@ struct PlaneShape {
   int PY;                     // LDS pitch of a row of N elements
   int threads;
   int padz;
+  int solve;                  // PCG solves take the pass (else vacuum solves and SC/PSD alone)
   size_t lds;                 // bytes
   FastDiv div_A2, div_nz, div_N, div_ny;
 };

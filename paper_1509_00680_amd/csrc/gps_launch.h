@@ -185,6 +185,9 @@ constexpr int kMaxFastLen = 448;     // longest length with two-level passes
 bool add_length_passes(const LengthPasses& e);
 bool fast_length(int L);
 int fast_xpass_parts(int L, int nrows);
+// 32-bit values that a thread of the FP32 solve's x inverse beside the plane pass holds
+// at once: row loads, operands of lout points per row, twiddles, partial sums.
+int fast_xinv_values(int L, int lout, int periodic_mean);
 template <typename T> int fast_strided_parts(const SParams<T>& p);   // z pass (solve mode)
 template <typename T> bool fast_strided(int mode, const SParams<T>& p, hipStream_t s);
 template <typename T> bool fast_xfwd(int mode, const XParams<T>& p, hipStream_t s);
