@@ -306,6 +306,23 @@ SParams<T> sparams(const gps_plan* pl, int axis, int L, int Lin, int Lout, int n
   return p;
 }
 
+// The plane pass's own memory is optional.  Where the device has no room for a call beside
+// it, the plan gives it back (tables and half spectra) and keeps to the y, z, y passes; the
+// half spectra are allocated last, when a call has all that it needs: by every call
+// where PCG solves take the pass, else by the vacuum solve and SC/PSD alone.
+bool give_back_plane(gps_plan* pl);
+
+template <typename F>
+void with_room(gps_plan* pl, F&& f) {
+  try {
+    f();
+    return;
+  } catch (const NoMem&) {
+    if (!give_back_plane(pl)) throw;
+  }
+  f();
+}
+
 // ---------------------------------------------------------------------------
 // plan-time Green's-function spectrum (FP64 on the device)
 // ---------------------------------------------------------------------------
@@ -336,19 +353,55 @@ GLRule gauss_legendre() {
   return r;
 }
 
-void build_green(gps_plan* pl) {
+size_t plane_table_count(const Geom& g) { return (size_t)g.Kx * g.Ly * (g.Lz / 2 + 1); }
+
+// Every table of the plan.  They come before build_green's transient spectrum: allocated
+// after it was freed, the plane tables were cut out of its block, and each next plan
+// waited for fresh blocks of both sizes (64^3: 0.26 -> 0.82 ms a plan).
+void alloc_tables(gps_plan* pl) {
   const Geom& g = pl->g;
-  hipStream_t s = pl->cap_stream;
   const size_t ntab = (size_t)(g.Lz / 2 + 1) * (g.Ly / 2 + 1) * g.Kx;
   dalloc(&pl->green64, ntab * sizeof(double), &pl->bytes);
   dalloc(&pl->green32, ntab * sizeof(float), &pl->bytes);
+  if (pl->bc == GPS_BC_PERIODIC) {
+    dalloc(&pl->lap64t, ntab * sizeof(double), &pl->bytes);
+    dalloc(&pl->lap32t, ntab * sizeof(float), &pl->bytes);
+  }
+  if (pl->compact) return;
+  pl->shape32 = plane_shape(g, sizeof(float));
+  pl->shape64 = plane_shape(g, sizeof(double));
+  try {
+    const size_t n = plane_table_count(g);
+    if (pl->shape32.N > 0) dalloc(&pl->plane32, n * sizeof(float), &pl->bytes);
+    if (pl->shape64.N > 0) dalloc(&pl->plane64, n * sizeof(double), &pl->bytes);
+  } catch (const NoMem&) {               // the y, z, y passes need neither
+    give_back_plane(pl);
+    pl->shape32.N = pl->shape64.N = 0;
+  }
+}
+
+// Device memory for the time of build_green, at the expense of the plane tables where the
+// device has no room for both.
+struct Transient {
+  void* p = nullptr;
+  Transient(gps_plan* pl, size_t bytes) {
+    size_t total = 0;
+    with_room(pl, [&] { dalloc(&p, bytes, &total); });
+  }
+  ~Transient() { dfree(p); }
+  Transient(const Transient&) = delete;
+  Transient& operator=(const Transient&) = delete;
+};
+
+void build_green(gps_plan* pl) {
+  const Geom& g = pl->g;
+  hipStream_t s = pl->cap_stream;
   const double norm = 1.0 / ((double)g.Lx * g.Ly * g.Lz);
   if (pl->bc == GPS_BC_FREE) {
     // K(m) on the full padded grid -> 3D FFT (FP64) -> fold and scale by h^3/N
     const size_t nfull = (size_t)g.Lz * g.Ly * g.Kx;
-    size_t tmp_bytes = 0;
-    cplx<double>* full = nullptr;
-    dalloc(&full, nfull * sizeof(cplx<double>), &tmp_bytes);
+    const Transient spectrum(pl, nfull * sizeof(cplx<double>));
+    cplx<double>* full = static_cast<cplx<double>*>(spectrum.p);
     XParams<double> xp = xparams<double>(pl, g.Ly * g.Lz, g.Ly, g.Lx, g.Lx,
                                          (long long)g.Ly * g.Kx, g.Lx);
     xp.work = full;
@@ -365,16 +418,14 @@ void build_green(gps_plan* pl) {
                           pl->green32, s);
     ck(hipGetLastError());
     ck(hipStreamSynchronize(s));
-    dfree(full);
   } else if (pl->bc == GPS_BC_WIRE) {
     // per z mode, the cell-averaged in-plane kernel on the (2ny, 2nx) padded
     // plane -> 2D FFT (FP64) -> fold and scale by h^2/N
     const size_t nfull = (size_t)g.Lz * g.Ly * g.Kx;
-    size_t tmp_bytes = 0;
-    cplx<double>* full = nullptr;
-    double* kt = nullptr;
-    dalloc(&full, nfull * sizeof(cplx<double>), &tmp_bytes);
-    dalloc(&kt, (size_t)g.Lz * g.Ly * g.Lx * sizeof(double), &tmp_bytes);
+    const Transient spectrum(pl, nfull * sizeof(cplx<double>));
+    const Transient kernel(pl, (size_t)g.Lz * g.Ly * g.Lx * sizeof(double));
+    cplx<double>* full = static_cast<cplx<double>*>(spectrum.p);
+    double* kt = static_cast<double*>(kernel.p);
     const double rw = 2.0 * g.h * std::sqrt((double)g.nx * g.nx + (double)g.ny * g.ny);
     launch_wire_gen(kt, g, rw, gauss_legendre(), s);
     XParams<double> xp = xparams<double>(pl, g.Ly * g.Lz, g.Ly, g.Lx, g.Lx,
@@ -389,14 +440,11 @@ void build_green(gps_plan* pl) {
     launch_compress_table(full, g.Kx, g.Ly, g.Lz, g.h * g.h * norm, pl->green64, pl->green32, s);
     ck(hipGetLastError());
     ck(hipStreamSynchronize(s));
-    dfree(full);
-    dfree(kt);
   } else if (pl->bc == GPS_BC_SURFACE) {
     const int Lyh = g.Ly / 2 + 1;
     const size_t nc = (size_t)g.Kx * Lyh;
-    size_t tmp_bytes = 0;
-    cplx<double>* buf = nullptr;
-    dalloc(&buf, nc * g.Lz * sizeof(cplx<double>), &tmp_bytes);
+    const Transient spectrum(pl, nc * g.Lz * sizeof(cplx<double>));
+    cplx<double>* buf = static_cast<cplx<double>*>(spectrum.p);
     // k_par = 0 kernel shifted by 2 pi Lz h (positive definite tent)
     launch_surface_gen(buf, g.Kx, Lyh, g.Lz, g.nx, g.ny, g.h, 2.0 * kPi * g.Lz * g.h, s);
     SParams<double> zp = sparams<double>(pl, 2, g.Lz, g.Lz, g.Lz / 2 + 1, (int)nc, (int)nc, 0,
@@ -406,11 +454,8 @@ void build_green(gps_plan* pl) {
     launch_surface_compress(buf, g.Kx, Lyh, g.Lz, g.h * norm, pl->green64, pl->green32, s);
     ck(hipGetLastError());
     ck(hipStreamSynchronize(s));
-    dfree(buf);
   } else {
     launch_periodic_table(g, 0, pl->green64, pl->green32, s);
-    dalloc(&pl->lap64t, ntab * sizeof(double), &pl->bytes);
-    dalloc(&pl->lap32t, ntab * sizeof(float), &pl->bytes);
     launch_periodic_table(g, 1, pl->lap64t, pl->lap32t, s);
     ck(hipGetLastError());
     ck(hipStreamSynchronize(s));
@@ -419,28 +464,14 @@ void build_green(gps_plan* pl) {
 
 // The Green's spectrum in the plane pass's order, for each precision that has
 // one (so that the tables do not depend on the precision chosen later).
-size_t plane_table_count(const Geom& g) { return (size_t)g.Kx * g.Ly * (g.Lz / 2 + 1); }
-
 void build_plane_tables(gps_plan* pl) {
   const Geom& g = pl->g;
-  if (pl->compact) return;
-  pl->shape32 = plane_shape(g, sizeof(float));
-  pl->shape64 = plane_shape(g, sizeof(double));
-  if (pl->shape32.N == 0 && pl->shape64.N == 0) return;
+  if (!pl->plane32 && !pl->plane64) return;
   plane_allow_lds();
-  try {
-    if (pl->shape32.N > 0) {
-      dalloc(&pl->plane32, plane_table_count(g) * sizeof(float), &pl->bytes);
-      launch_plane_table(pl->shape32, pl->green64, g.Kx, g.Ly, pl->plane32, pl->cap_stream);
-    }
-    if (pl->shape64.N > 0) {
-      dalloc(&pl->plane64, plane_table_count(g) * sizeof(double), &pl->bytes);
-      launch_plane_table(pl->shape64, pl->green64, g.Kx, g.Ly, pl->plane64, pl->cap_stream);
-    }
-  } catch (const NoMem&) {               // the y, z, y passes need neither table
-    if (!pl->plane32) pl->shape32.N = 0;
-    if (!pl->plane64) pl->shape64.N = 0;
-  }
+  if (pl->plane32)
+    launch_plane_table(pl->shape32, pl->green64, g.Kx, g.Ly, pl->plane32, pl->cap_stream);
+  if (pl->plane64)
+    launch_plane_table(pl->shape64, pl->green64, g.Kx, g.Ly, pl->plane64, pl->cap_stream);
   ck(hipGetLastError());
   ck(hipStreamSynchronize(pl->cap_stream));
 }
@@ -550,10 +581,6 @@ void grow_res(gps_plan* pl, bool need_ion, bool need_refine) {
   }
 }
 
-// The plane pass's own memory is optional.  Where the device has no room for a call beside
-// it, the plan gives it back (tables and half spectra) and keeps to the y, z, y passes; the
-// half spectra are allocated last, when a call has all that it needs: by every call
-// where PCG solves take the pass, else by the vacuum solve and SC/PSD alone.
 template <typename T>
 void free_half(Res<T>& R, const Geom& g) {
   for (int i = 0; i < R.nslots; ++i) {
@@ -561,19 +588,6 @@ void free_half(Res<T>& R, const Geom& g) {
     dfree(R.slot(i).half);
     R.bytes -= (size_t)g.nz * g.ny * g.Kx * sizeof(cplx<T>);
   }
-}
-
-bool give_back_plane(gps_plan* pl);
-
-template <typename F>
-void with_room(gps_plan* pl, F&& f) {
-  try {
-    f();
-    return;
-  } catch (const NoMem&) {
-    if (!give_back_plane(pl)) throw;
-  }
-  f();
 }
 
 template <typename T>
@@ -1747,6 +1761,7 @@ static gps_status plan_create(int nx, int ny, int nz, double h, int bc, bool com
       ck(hipMemcpyAsync(pl->tw32[a], t32[a].data(), t32[a].size() * sizeof(float),
                         hipMemcpyHostToDevice, pl->cap_stream));
     }
+    alloc_tables(pl);
     build_green(pl);   // synchronizes cap_stream (the host twiddles outlive the copies)
     build_plane_tables(pl);
   } catch (const NoMem&) {

@@ -14,7 +14,8 @@
 
 namespace fake {
 inline std::map<void*, size_t> blocks;         // device allocations
-inline size_t used = 0, limit = ~size_t(0);
+inline size_t used = 0, peak = 0, limit = ~size_t(0);
+inline int frees = 0, late = 0;                // frees, and allocations after one
 inline std::map<std::string, int> launches;    // by kernel name (mangled)
 // (the library registers its kernels before this executable's objects are constructed)
 inline std::map<const void*, std::string>& names() {
@@ -78,12 +79,15 @@ hipError_t hipMalloc(void** p, size_t n) {
   *p = std::calloc(n, 1);
   fake::blocks[*p] = n;
   fake::used += n;
+  if (fake::used > fake::peak) fake::peak = fake::used;
+  if (fake::frees > 0) ++fake::late;
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {
   const auto b = fake::blocks.find(p);
   if (p == nullptr) return hipSuccess;
   if (b == fake::blocks.end()) std::abort();
+  ++fake::frees;
   fake::used -= b->second;
   fake::blocks.erase(b);
   std::free(p);

@@ -125,6 +125,33 @@ static void run(int bc, const Kind& k) {
   }
 }
 
+// A plan is made within the bytes that one without the pass needs at the most, and allocates
+// nothing after it has freed its transient (the next plan then finds both blocks again).
+static void create(int bc) {
+  gps_plan* p = nullptr;
+  fake::limit = ~size_t(0);
+  fake::peak = 0;
+  EXPECT(gps::compact_plan_create(N, N, N, 0.5, bc, &p) == GPS_OK, "bc %d", bc);
+  gps_plan_destroy(p);
+  const size_t least = fake::peak;
+  fake::peak = 0;
+  fake::frees = fake::late = 0;
+  EXPECT(gps_plan_create(N, N, N, 0.5, bc, &p) == GPS_OK, "bc %d", bc);
+  EXPECT(fake::late == 0, "bc %d: %d allocations after a free", bc, fake::late);
+  gps_plan_destroy(p);
+  const size_t most = fake::peak;
+  EXPECT(most > least, "bc %d", bc);
+  for (int i = 0; i <= 16; ++i) {
+    fake::limit = least + (most - least) * i / 16;
+    EXPECT(gps_plan_create(N, N, N, 0.5, bc, &p) == GPS_OK, "bc %d: limit %d of 16", bc, i);
+    gps_plan_destroy(p);
+    EXPECT(fake::used == 0, "bc %d: leak", bc);
+    fake::limit = least * (i + 1) / 18;
+    EXPECT(gps_plan_create(N, N, N, 0.5, bc, &p) == GPS_E_NOMEM, "bc %d: %d of 18", bc, i);
+    EXPECT(p == nullptr && fake::used == 0, "bc %d: leak", bc);
+  }
+}
+
 // An FP64 server whose budget holds two plans without the pass keeps both.
 static void serve_fp64(int bc) {
   fake::limit = ~size_t(0);
@@ -206,6 +233,7 @@ int main() {
       run(bc, k);
     }
   for (int bc : {GPS_BC_FREE, GPS_BC_SURFACE, GPS_BC_PERIODIC, GPS_BC_WIRE}) {
+    create(bc);
     serve_fp64(bc);
     size_t t0 = 0, b0 = 0, t1 = 0, b1 = 0;
     gps_plan_footprint(N, N, N, bc, GPS_PREC_FP64, 20, 0, 0, &t0, &b0, nullptr);
