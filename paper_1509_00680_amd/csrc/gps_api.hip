@@ -38,10 +38,6 @@ struct TimedLaunch {
   hipEvent_t start, stop;
 };
 
-struct DevError {
-  hipError_t e;
-};
-
 inline void ck(hipError_t e) {
   if (e != hipSuccess) throw DevError{e};
 }

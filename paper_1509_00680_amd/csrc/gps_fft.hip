@@ -448,6 +448,11 @@ template <typename T> int xpass_parts(const XParams<T>& p) {
 }
 
 template <typename T> void launch_xfwd(int mode, const XParams<T>& p, hipStream_t s) {
+  if (p.sh.N > 0) {                    // the generic passes know no planes
+    if (!fast_length(p.g.Lx) || !fast_xfwd<T>(mode, p, s))
+      throw DevError{hipErrorInvalidConfiguration};
+    return;
+  }
   if (mode != XF_GEN_FREE && fast_length(p.g.Lx) && fast_xfwd<T>(mode, p, s)) return;
   const dim3 grid(generic_xpass_groups(p), p.has_slots ? p.batch.n : 1);
   const size_t lds = (size_t)p.P * p.g.Lx * sizeof(cplx<T>);
@@ -457,6 +462,11 @@ template <typename T> void launch_xfwd(int mode, const XParams<T>& p, hipStream_
 }
 
 template <typename T> void launch_xinv(int mode, const XParams<T>& p, hipStream_t s) {
+  if (p.sh.N > 0) {
+    if (!fast_length(p.g.Lx) || !fast_xinv<T>(mode, p, s))
+      throw DevError{hipErrorInvalidConfiguration};
+    return;
+  }
   if (fast_length(p.g.Lx) && fast_xinv<T>(mode, p, s)) return;
   const dim3 grid(generic_xpass_groups(p), p.has_slots ? p.batch.n : 1);
   const size_t lds = (size_t)p.P * p.g.Lx * sizeof(cplx<T>);
@@ -612,6 +622,7 @@ void plane_allow_lds() {
 }
 
 template <typename T> void launch_plane(const PlaneParams<T>& p, hipStream_t s) {
+  if (sizeof(T) != sizeof(float) && !p.work) throw DevError{hipErrorInvalidConfiguration};
   const dim3 grid(plane_groups(p.Kx) + (p.sc.st ? 1 : 0), p.work ? 1 : p.batch.n);
   const dim3 blk(p.sh.threads);
   if (p.sh.padz) GPS_LAUNCH((k_plane<T, true>), grid, blk, p.sh.lds, s, p);

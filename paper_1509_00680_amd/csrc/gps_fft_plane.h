@@ -76,13 +76,15 @@ __global__ __launch_bounds__(plane_threads(sizeof(T))) void k_plane(PlaneParams<
   cplx<T>* work = p.work;
   const SolveState* st = nullptr;
   double* part_delta = nullptr;
-  if (work == nullptr) {
-    const Slot<T> sl = p.tab.s[p.batch.slot[blockIdx.y]];
-    half = sl.half;
-    work = sl.work;
-    st = sl.st;
-    part_delta = sl.part_delta;
-    if (solve_stopped(st)) return;
+  if constexpr (sizeof(T) == sizeof(float)) {     // PCG solves: FP32 alone
+    if (work == nullptr) {
+      const Slot<T> sl = p.tab.s[p.batch.slot[blockIdx.y]];
+      half = sl.half;
+      work = sl.work;
+      st = sl.st;
+      part_delta = sl.part_delta;
+      if (solve_stopped(st)) return;
+    }
   }
   const int t = xcd_tile(blockIdx.x, gridDim.x) - dec;   // the two of one kx meet in one L2
   const int kx = t >> 1, r = t & 1;
@@ -180,7 +182,8 @@ __global__ __launch_bounds__(plane_threads(sizeof(T))) void k_plane(PlaneParams<
         const int kz = k1 + C1 * i;
         gm[i] = tt[min(kz, Lz - kz) * N + y];
       }
-      if (k0_from_slot && t == 0 && job == 0) gm[0] = T(st->g0);
+      if constexpr (sizeof(T) == sizeof(float))
+        if (k0_from_slot && t == 0 && job == 0) gm[0] = T(st->g0);
       cplx<T>* d = tile + (R * k1) * PY + y;
       cplx<T> x[R];
 #pragma unroll

@@ -898,7 +898,7 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
   // The x passes exist for full rows (PAD = false) and for half-padded rows
   // (PAD: L/2 points), the periodic mean term on full rows only (a padded x
   // axis is not periodic); beside the plane pass there is no refinement
-  // and no FP64 solve.
+  // and no FP64 solve (beside_plane).
   template <typename T, bool PAD>
   static void xfwd_p(int mode, const XParams<T>& p, dim3 grid, hipStream_t s) {
     const dim3 blk(xthreads(L1, L2, P));
@@ -962,8 +962,13 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
     return dim3(((p.nrows + 1) / 2 + P - 1) / P, p.has_slots ? p.batch.n : 1);
   }
 
+  template <typename T> static bool beside_plane(bool solve, const XParams<T>& p) {
+    return L <= kPlaneMaxLx && (!solve || (sizeof(T) == sizeof(float) && !p.refine));
+  }
+
   template <typename T> static bool xfwd(int mode, const XParams<T>& p, hipStream_t s) {
     if (mode != XF_SOLVE && mode != XF_REAL) return false;
+    if (p.sh.N > 0 && !beside_plane(mode == XF_SOLVE, p)) return false;
     if (p.in_row_stride != p.Lin) return false;        // the kernels assume contiguous rows
     if (p.Lin == L) {
       xfwd_p<T, false>(mode, p, xgrid(p), s);
@@ -979,6 +984,7 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
   }
 
   template <typename T> static bool xinv(int mode, const XParams<T>& p, hipStream_t s) {
+    if (p.sh.N > 0 && !beside_plane(mode == XI_SOLVE, p)) return false;
     if (p.in_row_stride != p.Lout) return false;       // the kernels assume contiguous rows
     if (p.Lout == L) {
       xinv_p<T, false>(mode, p, xgrid(p), s);

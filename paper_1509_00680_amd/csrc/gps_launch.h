@@ -8,6 +8,13 @@
 
 namespace gps {
 
+// A failed HIP call, or a launch that the library has no kernel for (a defect of
+// the library, reported as a device error rather than run).  Thrown by launchers and
+// caught by every entry point that launches.
+struct DevError {
+  hipError_t e;
+};
+
 // ---- timed launches ---------------------------------------------------------
 
 // Events that the next launch made on this host thread binds to its dispatch
@@ -102,6 +109,8 @@ template <typename T> struct XParams {
 enum XinvMode { XI_SOLVE = 0, XI_REAL = 1, XI_SOLVE_PERIODIC = 2 };
 constexpr int XI_SOLVE_REF = 3;
 
+// Beside the plane pass (sh.N > 0) XF_REAL / XI_REAL and the FP32 XF_SOLVE / XI_SOLVE
+// without refinement exist, at x lengths up to kPlaneMaxLx; DevError for any other.
 template <typename T> void launch_xfwd(int mode, const XParams<T>& p, hipStream_t s);
 template <typename T> void launch_xinv(int mode, const XParams<T>& p, hipStream_t s);
 // Partial sums written by a solve-mode x pass, whichever family runs (at most
@@ -158,6 +167,7 @@ template <typename T> struct PlaneParams {
 };
 // The plane pass of a grid (elem: bytes of the bulk type), N = 0 if it has none.
 PlaneShape plane_shape(const Geom& g, size_t elem);
+// In slots (work null) FP32 alone.
 template <typename T> void launch_plane(const PlaneParams<T>& p, hipStream_t s);
 // Lets the plane kernels use a CU's whole LDS on the current device.
 void plane_allow_lds();
