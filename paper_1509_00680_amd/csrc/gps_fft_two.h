@@ -46,6 +46,17 @@ constexpr bool kept_roots(int L) {
          L == 320 || L == 384;
 }
 
+// The passes address their buffers with 32-bit byte offsets, and multiply a stride by a
+// small count with a 24-bit product.  One axis has at most kMaxFastLen points, the others
+// kMaxLen, so the largest buffers (FP64 half spectra, with the short axis along x or not, and
+// FP64 fields) stay below 4 GiB and the z pass's strides below 2^24.
+constexpr long long kMaxOffset = 1ll << 32;
+static_assert(16ll * kMaxLen * kMaxFastLen * (kMaxLen / 2 + 1) <= kMaxOffset, "work buffer");
+static_assert(16ll * kMaxLen * kMaxLen * (kMaxFastLen / 2 + 1) <= kMaxOffset, "work buffer");
+static_assert(8ll * kMaxLen * kMaxLen * kMaxFastLen <= kMaxOffset, "field");
+static_assert(16ll * kMaxLen * (kMaxLen / 2 + 1) < (1 << 24), "stride of the z pass");
+static_assert(8ll * (kMaxLen / 2 + 1) * (kMaxLen / 2 + 1) < (1 << 24), "stride of its table");
+
 template <typename T>
 __device__ __forceinline__ cplx<T> cconj(cplx<T> a) { return cmk(a.x, -a.y); }
 
@@ -114,14 +125,13 @@ void k_fstrided(SParams<T> p) {
   // (xcd_tile maps work-group 0 to tile 0, so the shift keeps every XCD's
   // tiles contiguous)
   const int tile0 = (xcd_tile(blockIdx.x, gridDim.x) - dec) * NTILE;
-  // 32-bit byte offsets: the longest compile-time length is 384, so every
-  // buffer these passes index is below 4 GiB
+  // 32-bit byte offsets (checked beside kMaxOffset)
   constexpr unsigned CB = sizeof(cplx<T>);
   const unsigned es = CB * (unsigned)p.elem_stride;
   // Element e of this thread's pencil sits at base + e * es.  Every element a
   // thread touches has e = q + L1 k or e = q + L2 k (k compile-time), so its
   // offset is qb + k * (L1 es) or qb + k * (L2 es): one per-thread product
-  // (es < 2^24 for every compile-time length) and scalar steps.
+  // (es < 2^24) and scalar steps.
   const unsigned s1 = (unsigned)L1 * es, s2 = (unsigned)L2 * es;
   int pen[NTILE];
   bool pv[NTILE];
@@ -367,7 +377,7 @@ struct RowCol {
 };
 
 // Element idx of a buffer with a work-group-uniform base, addressed through a
-// 32-bit byte offset (the buffers of the compile-time lengths are < 4 GiB).
+// 32-bit byte offset (checked beside kMaxOffset).
 #define GPS_AT(ptr, idx) at_bytes((ptr), (unsigned)(idx) * (unsigned)sizeof(*(ptr)))
 
 // Work-buffer offsets of the NR consecutive rows row0, row0 + 1, ... of a
