@@ -328,7 +328,10 @@ gps_status gps_last_history(const gps_plan *plan, double *out, int max_entries);
  * decision) are accumulated.
  * Untimed solves replay the iterations as captured HIP graphs; timed solves
  * launch the same kernels one by one (events inside a graph are not
- * readable), so a timed solve is slower end to end than an untimed one.
+ * readable), so a timed solve is slower end to end than an untimed one.  Where
+ * a solve runs its y and z passes as one kernel (the plane pass), GPS_K_ZCONV
+ * times that kernel, and a solve timed for GPS_K_YFWD or GPS_K_YINV runs the y,
+ * z and y passes instead, so that there is a y pass to time.
  * GPS_K_NONE switches timing off.  Setting a kind clears the totals.
  * Errors: GPS_E_INVALID (null plan, unknown kind). */
 typedef enum {

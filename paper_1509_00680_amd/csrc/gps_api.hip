@@ -728,9 +728,24 @@ void collect_timing(gps_plan* pl, const std::vector<TimedLaunch>& ev, int k_base
   }
 }
 
+// Whether the vacuum solver of this plan runs as x, plane, x.  A solve with
+// refinement keeps the y, z, y passes (its FP64 sources live in their x
+// passes), and so does a timed y pass.  So do PCG solves where the shape says
+// so (PlaneShape::solve), all FP64 ones among them: PCG multiplies a change of
+// rounding by up to 1e8 (solutions of 32^3 to 64^3 at 1e-6 differ by 1e-8), and
+// FP64 results are to stay what they are.
+template <typename T>
+bool use_plane(gps_plan* pl, int refine) {
+  return pl->shape<T>().N > 0 && pl->res<T>().slot().half && !refine &&
+         pl->timing_kind != GPS_K_YFWD && pl->timing_kind != GPS_K_YINV;
+}
+
 // Algorithmic bytes of one launch of pass `kind` (inputs read once, outputs
-// written once), bulk element size s.
-double pass_bytes(const gps_plan* pl, int kind, size_t s) {
+// written once) of a PCG solve in T.
+template <typename T>
+double pass_bytes(gps_plan* pl, int kind, int refine) {
+  const size_t s = sizeof(T);
+  const bool plane = pl->shape<T>().solve && use_plane<T>(pl, refine);
   const Geom& g = pl->g;
   const double n = (double)pl->npts();
   const double c = 2.0 * s;
@@ -741,18 +756,14 @@ double pass_bytes(const gps_plan* pl, int kind, size_t s) {
   switch (kind) {
     case GPS_K_XFWD: return (5.0 * s + 16.0) * n + rows * g.Kx * c;   // with the fused update
     case GPS_K_YFWD: return (double)g.nz * g.Kx * g.ny * c + wbox * c;
-    case GPS_K_ZCONV: {
-      if (s == sizeof(float) && pl->shape32.N > 0 && pl->shape32.solve)   // plane pass
+    case GPS_K_ZCONV:
+      if (plane)
         return (double)g.nz * g.ny * g.Kx * c + wbox * c +
                (double)(g.Lz / 2 + 1) * g.Ly * g.Kx * s;
       return 2.0 * wbox * c + tab * s;
-    }
     case GPS_K_YINV: return wbox * c + (double)g.nz * g.Kx * g.ny * c;
-    case GPS_K_XINV: {                                // with the direction update
-      const bool plane = s == sizeof(float) && pl->shape32.N > 0 && pl->shape32.solve;
-      const double in = plane ? wbox : rows * g.Kx;
-      return in * c + (7.0 + periodic) * n * s;
-    }
+    case GPS_K_XINV:                                  // with the direction update
+      return (plane ? wbox : rows * g.Kx) * c + (7.0 + periodic) * n * s;
     default: return 0.0;
   }
 }
@@ -760,18 +771,6 @@ double pass_bytes(const gps_plan* pl, int kind, size_t s) {
 // ---------------------------------------------------------------------------
 // one PCG iteration for the problems of a batch (all of one plan)
 // ---------------------------------------------------------------------------
-// Whether the vacuum solver of this plan runs as x, plane, x.  A solve with
-// refinement keeps the y, z, y passes (its FP64 sources live in their x
-// passes), and so does a timed y pass.  So do PCG solves where the shape says
-// so (PlaneShape::solve), all FP64 ones among them: PCG multiplies a change of
-// rounding by up to 1e8 (solutions of 32^3 to 64^3 at 1e-6 differ by 1e-8), and
-// FP64 results are to stay what they are.
-template <typename T>
-bool use_plane(gps_plan* pl, int refine) {
-  return pl->shape<T>().N > 0 && pl->res<T>().slot().half && !refine && pl->timing_kind != GPS_K_YFWD &&
-         pl->timing_kind != GPS_K_YINV;
-}
-
 template <typename T>
 PlaneParams<T> plane_params(const gps_plan* pl, const T* table) {
   PlaneParams<T> p{};
@@ -1044,7 +1043,7 @@ SolveState run_pcg(gps_plan* pl, int check_neutral, const double* track_rho = nu
       // nonlinear outer loop had stopped before this solve (the state still
       // holds the previous inner solve, and every launch returned at once)
       collect_timing(pl, pl->ev_pending, k_base, st.outer_done ? 0 : st.done ? st.iters : k);
-      pl->timing_bytes = pass_bytes(pl, pl->timing_kind, sizeof(T));
+      pl->timing_bytes = pass_bytes<T>(pl, pl->timing_kind, track);
     }
     if (st.done || k > pl->opt.maxit + 1) break;
     if (m > 0 && k == next_ref) {         // every iteration so far did work

@@ -125,6 +125,31 @@ static void run(int bc, const Kind& k) {
   }
 }
 
+// A timed pass reports the bytes of the kernel that ran: the plane pass's where the solve
+// takes it, else (refinement, a timed y pass, a plan without it) those of the three passes.
+static void timed(int refine) {
+  fake::limit = ~size_t(0);
+  const Kind k{"timed", GPS_PREC_MIXED, true, refine, nullptr};
+  for (int kind : {GPS_K_XFWD, GPS_K_YFWD, GPS_K_ZCONV, GPS_K_YINV, GPS_K_XINV}) {
+    double bytes[2];
+    bool planes[2];
+    for (int compact = 0; compact < 2; ++compact) {
+      gps_plan* p = make(GPS_BC_FREE, k, compact);
+      EXPECT(gps_plan_set_timing(p, kind) == GPS_OK, "timing");
+      fake::launches.clear();
+      EXPECT(gps_solve_generalized(p, rho.data(), eps.data(), phi.data(), 1e-6) == GPS_OK, "timed");
+      planes[compact] = fake::count("k_plane") > fake::count("k_plane_table");
+      EXPECT(gps_plan_timing(p, nullptr, nullptr, &bytes[compact]) == GPS_OK, "timing");
+      gps_plan_destroy(p);
+    }
+    const bool y = kind == GPS_K_YFWD || kind == GPS_K_YINV;
+    EXPECT(!planes[1] && planes[0] == (!refine && !y), "kind %d, refine %d: route", kind, refine);
+    const bool differs = planes[0] && (kind == GPS_K_ZCONV || kind == GPS_K_XINV);
+    EXPECT((bytes[0] != bytes[1]) == differs && bytes[1] > 0.0, "kind %d, refine %d: bytes %g, %g",
+           kind, refine, bytes[0], bytes[1]);
+  }
+}
+
 // A plan is made within the bytes that one without the pass needs at the most, and allocates
 // nothing after it has freed its transient (the next plan then finds both blocks again).
 static void create(int bc) {
@@ -232,6 +257,8 @@ int main() {
       if (periodic && (k.refine > 0 || std::strncmp(k.name, "sc", 2) == 0)) continue;
       run(bc, k);
     }
+  timed(0);
+  timed(5);
   for (int bc : {GPS_BC_FREE, GPS_BC_SURFACE, GPS_BC_PERIODIC, GPS_BC_WIRE}) {
     create(bc);
     serve_fp64(bc);
