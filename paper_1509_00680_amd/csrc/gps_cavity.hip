@@ -92,9 +92,11 @@ __global__ __launch_bounds__(kThreads) void k_rigid_cavity(Geom g, int nbx, int 
       if (g.periodic_y) dy -= ly * rint(dy / ly);
       if (g.periodic_z) dz -= lz * rint(dz / lz);
       const double r = sqrt(dx * dx + dy * dy + dz * dz);
-      // (a relative margin for the rounding of both sides)
-      is_near = r * (1.0 - 1e-12) - reach <= (ad + kFarT * delta) * (1.0 + 1e-12) +
-                                                 1e-12 * (fabs(ax) + fabs(ay) + fabs(az));
+      // (a relative margin for the rounding of both sides; where r overflows, the points
+      // decide for themselves)
+      is_near = !isfinite(r) ||
+                r * (1.0 - 1e-12) - reach <= (ad + kFarT * delta) * (1.0 + 1e-12) +
+                             1e-12 * (fabs(ax) + fabs(ay) + fabs(az));
     }
     const unsigned long long mask = __ballot(is_near);
     const int lane = tid & 63, wave = tid >> 6;
