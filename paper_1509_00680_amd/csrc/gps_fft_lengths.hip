@@ -37,7 +37,7 @@ constexpr int even_pairs(int m) {
 
 #define GPS_LENGTH(A, B)           \
   static const bool len_##A##_##B = \
-      add_length_passes(TwoLevel<A, B, even_pairs(larger(A, B)), false>::passes());
+      add_length<A, B, even_pairs(larger(A, B)), false>();
 
 #if GPS_LENGTH_GROUP == 0
 GPS_LENGTH(4, 5)

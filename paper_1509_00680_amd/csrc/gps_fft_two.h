@@ -1009,6 +1009,12 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
     return false;
   }
 
+  // The FP32 x passes alone (grids of few rows).
+  static LengthPasses x_passes32() {
+    return LengthPasses{L, L1, L2, P, nullptr, nullptr, &TwoLevel::template xfwd<float>, nullptr,
+                        &TwoLevel::template xinv<float>, nullptr};
+  }
+
   static LengthPasses passes() {
     return LengthPasses{L, L1, L2, P,
                         &TwoLevel::template strided<float>, &TwoLevel::template strided<double>,
@@ -1016,5 +1022,13 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
                         &TwoLevel::template xinv<float>, &TwoLevel::template xinv<double>};
   }
 };
+
+// Adds the entries of a length.
+template <int L1, int L2, int P, bool TUNED> bool add_length() {
+  bool ok = add_length_passes(TwoLevel<L1, L2, P, TUNED>::passes());
+  if constexpr (L1 * L2 <= kFewRowsLen)
+    ok = add_few_rows_passes(TwoLevel<L1, L2, kFewRowsPairs, TUNED>::x_passes32()) && ok;
+  return ok;
+}
 
 }  // namespace gps

@@ -193,8 +193,12 @@ struct LengthPasses {
 };
 constexpr int kMaxFastLen = 448;     // longest length with two-level passes
 bool add_length_passes(const LengthPasses& e);
+// Lengths up to kFewRowsLen take their FP32 x passes from a second entry on grids of up
+// to kFewRows rows (gps_fft_fast.hip).
+constexpr int kFewRows = 4096, kFewRowsLen = 64, kFewRowsPairs = 4;
+bool add_few_rows_passes(const LengthPasses& e);
 bool fast_length(int L);
-int fast_xpass_parts(int L, int nrows);
+template <typename T> int fast_xpass_parts(int L, int nrows);
 // 32-bit values that a thread of the FP32 solve's x inverse beside the plane pass holds
 // at once: row loads, operands of lout points per row, twiddles, partial sums.
 int fast_xinv_values(int L, int lout, int periodic_mean);

@@ -15,8 +15,11 @@ def lengths(shape, bc):
     return (nx if pxy else 2 * nx), (ny if pxy else 2 * ny), (nz if pz else 2 * nz)
 
 
-def row_pairs(L):
+def row_pairs(L, rows=None, elem=8):
+    """Row pairs of an x-pass work-group; rows None: a grid of many rows."""
     a, b = SPLITS[L]
+    if elem == 4 and L <= 64 and rows is not None and rows <= 4096:
+        return 4
     return ib.X_PAIRS(a) if L in ib.FAST else even_pairs(max(a, b))
 
 

@@ -10,13 +10,15 @@ from test_fft_lengths import SPLITS
 
 
 @pytest.mark.parametrize("L", sorted(SPLITS))
-def test_row_pairs_depend_on_the_length_alone(L):
-    """Row pairs per x-pass work-group: one count per length (a rule of its factors), at every
-    number of rows and in both precisions."""
-    P = plane_rule.row_pairs(L)
-    parts = gps.load()["_ZN3gps16fast_xpass_partsEii"]     # gps::fast_xpass_parts(int, int)
+@pytest.mark.parametrize("elem", [4, 8])
+def test_row_pairs(L, elem):
+    """Row pairs per x-pass work-group: by the length's factors, but four in FP32 at every length
+    up to 64 on grids of up to 4096 rows."""
+    # gps::fast_xpass_parts<T>(int, int)
+    parts = gps.load()["_ZN3gps16fast_xpass_partsI%sEEiii" % {4: "f", 8: "d"}[elem]]
     parts.restype, parts.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.c_int]
     for rows in (4, 81, 900, 1024, 4095, 4096, 4097, 25600):
+        P = plane_rule.row_pairs(L, rows, elem)
         assert parts(L, rows) == -(-((rows + 1) // 2) // P), rows
 
 

@@ -106,6 +106,22 @@ def test_full_rows_beside_both_routes(L):
             _three_iterations(shape, "periodic", precision, rho, eps)
 
 
+@pytest.mark.parametrize("L", [L for L in sorted(SPLITS) if L <= 64])
+def test_short_rows_on_both_sides_of_the_row_count(L):
+    """Up to 64 points a row the FP32 x passes take four row pairs per work-group on few rows and
+    the length's own count on many; full and padded rows."""
+    require_gpu()
+    for bc, n in (("periodic", L),) + ((("free", L // 2),) if L % 2 == 0 else ()):
+        for shape, few in (((63, 64, n), True), ((70, 60, n), False)):
+            rows = shape[0] * shape[1]
+            assert (plane_rule.row_pairs(L, rows, 4) == 4) == few
+            rho, eps = _fields(shape, bc, L)
+            expect = green.VacuumSolver(shape, 0.45, bc).apply(rho)
+            print("rows", shape, bc, flush=True)
+            _vacuum(shape, bc, "mixed", rho, expect)
+            _three_iterations(shape, bc, "mixed", rho, eps)
+
+
 # shape, boundary condition, element, PCG solves take it
 TILES = [((96, 96, 80), "free", 4, True), ((98, 98, 98), "free", 4, True),
          ((64, 64, 64), "free", 8, False), ((63, 63, 63), "free", 8, False),
