@@ -793,10 +793,10 @@ void enqueue_iteration(gps_plan* pl, const SlotTable<T>& tab, const Batch& b, in
   xp.tab = tab;
   xp.has_slots = 1;
   xp.batch = b;
-  xp.n_pap_parts = xpass_parts(xp);
   xp.refine = refine;
-  check_parts(xp.n_pap_parts, part_caps(g).x);
   xp.periodic_mean = periodic;
+  xp.n_pap_parts = xpass_parts(xp);
+  check_parts(xp.n_pap_parts, part_caps(g).x);
   if constexpr (sizeof(T) == sizeof(float)) {
     if (pl->shape<T>().solve && use_plane<T>(pl, refine)) {
       xp.sh = pl->shape<T>();

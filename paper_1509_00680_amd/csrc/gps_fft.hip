@@ -443,7 +443,7 @@ template <typename T> static int generic_xpass_groups(const XParams<T>& p) {
 // Partials of the solve-mode x passes: one per wavefront in the two-level
 // passes, one per work-group in the generic ones.
 template <typename T> int xpass_parts(const XParams<T>& p) {
-  if (fast_length(p.g.Lx)) return fast_xpass_parts<T>(p.g.Lx, p.nrows);
+  if (fast_solve(p)) return fast_xpass_parts<T>(p.g.Lx, p.nrows);
   return generic_xpass_groups(p);
 }
 

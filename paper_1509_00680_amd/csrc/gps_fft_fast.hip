@@ -57,6 +57,14 @@ template <typename T> static const LengthPasses& x_passes(int L, int nrows) {
   return g_passes[L];
 }
 
+template <typename T> bool fast_solve(const XParams<T>& p) {
+  if (!fast_length(p.g.Lx)) return false;
+  return sizeof(T) == sizeof(float) || g_passes[p.g.Lx].six64 || p.Lin != p.g.Lx ||
+         !(p.refine || p.periodic_mean);
+}
+template bool fast_solve<float>(const XParams<float>&);
+template bool fast_solve<double>(const XParams<double>&);
+
 // Partials of the solve-mode x passes: one per work-group.
 template <typename T> int fast_xpass_parts(int L, int nrows) {
   const int P = x_passes<T>(L, nrows).P;

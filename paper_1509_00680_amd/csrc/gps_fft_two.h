@@ -925,7 +925,8 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
       }
     }
     if (mode == XF_SOLVE && p.refine) {
-      GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_SOLVE_REF, PAD, false>), grid, blk, 0, s, p);
+      if constexpr (six_fit<T, PAD>())
+        GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_SOLVE_REF, PAD, false>), grid, blk, 0, s, p);
     } else if (mode == XF_SOLVE) {
       GPS_LAUNCH((k_fxfwd<T, L1, L2, P, XF_SOLVE, PAD, false>), grid, blk, 0, s, p);
     } else {
@@ -939,13 +940,13 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
       GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_REAL, PAD, PLANE>), grid, blk, 0, s, p);
       return;
     }
-    if constexpr (!PAD) {
+    if constexpr (!PAD && six_fit<T, PAD>()) {
       if (mode == XI_SOLVE && p.periodic_mean) {
         GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_SOLVE_PERIODIC, PAD, PLANE>), grid, blk, 0, s, p);
         return;
       }
     }
-    if constexpr (!PLANE) {
+    if constexpr (!PLANE && six_fit<T, PAD>()) {
       if (mode == XI_SOLVE && p.refine) {
         GPS_LAUNCH((k_fxinv<T, L1, L2, P, XI_SOLVE_REF, PAD, PLANE>), grid, blk, 0, s, p);
         return;
@@ -972,6 +973,20 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
     return dim3(((p.nrows + 1) / 2 + P - 1) / P, p.has_slots ? p.batch.n : 1);
   }
 
+  // A thread of the solve's x inverse holds 4 P KI values of the rows and its points'
+  // fields.  FP64 solves with six fields on full rows of 324, 378, 400, 420 and 432 points (544 to
+  // 576 registers, 528 at 378) spill 44 to 126 of 512, and were slower than the generic passes:
+  // periodic 0.90 to 0.97 x (378: 0.996), refined 0.85 to 0.98.  At up to 504 (360: 40 spilled)
+  // the two-level ones win: 1.05 to 1.2.
+  template <typename T, bool PAD> static constexpr bool six_fit() {
+    constexpr int NT = xthreads(L1, L2, P), Lout = PAD ? L / 2 : L;
+    constexpr int KI = (L / 2 + 1 + NT - 1) / NT, EOUT = (2 * P * Lout + NT - 1) / NT;
+    return int(sizeof(T) / 4) * (4 * P * KI + 6 * EOUT) < 528;
+  }
+  template <typename T> static bool six_fields(const XParams<T>& p) {
+    return p.refine || p.periodic_mean;
+  }
+
   template <typename T> static bool beside_plane(bool solve, const XParams<T>& p) {
     return L <= kPlaneMaxLx && (!solve || (sizeof(T) == sizeof(float) && !p.refine));
   }
@@ -981,6 +996,7 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
     if (p.sh.N > 0 && !beside_plane(mode == XF_SOLVE, p)) return false;
     if (p.in_row_stride != p.Lin) return false;        // the kernels assume contiguous rows
     if (p.Lin == L) {
+      if (mode == XF_SOLVE && six_fields(p) && !six_fit<T, false>()) return false;
       xfwd_p<T, false>(mode, p, xgrid(p), s);
       return true;
     }
@@ -997,6 +1013,7 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
     if (p.sh.N > 0 && !beside_plane(mode == XI_SOLVE, p)) return false;
     if (p.in_row_stride != p.Lout) return false;       // the kernels assume contiguous rows
     if (p.Lout == L) {
+      if (mode == XI_SOLVE && six_fields(p) && !six_fit<T, false>()) return false;
       xinv_p<T, false>(mode, p, xgrid(p), s);
       return true;
     }
@@ -1011,12 +1028,12 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
 
   // The FP32 x passes alone (grids of few rows).
   static LengthPasses x_passes32() {
-    return LengthPasses{L, L1, L2, P, nullptr, nullptr, &TwoLevel::template xfwd<float>, nullptr,
+    return LengthPasses{L, L1, L2, P, false, nullptr, nullptr, &TwoLevel::template xfwd<float>, nullptr,
                         &TwoLevel::template xinv<float>, nullptr};
   }
 
   static LengthPasses passes() {
-    return LengthPasses{L, L1, L2, P,
+    return LengthPasses{L, L1, L2, P, six_fit<double, false>(),
                         &TwoLevel::template strided<float>, &TwoLevel::template strided<double>,
                         &TwoLevel::template xfwd<float>, &TwoLevel::template xfwd<double>,
                         &TwoLevel::template xinv<float>, &TwoLevel::template xinv<double>};

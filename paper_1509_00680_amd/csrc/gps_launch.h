@@ -115,6 +115,7 @@ template <typename T> void launch_xfwd(int mode, const XParams<T>& p, hipStream_
 template <typename T> void launch_xinv(int mode, const XParams<T>& p, hipStream_t s);
 // Partial sums written by a solve-mode x pass, whichever family runs (at most
 // the number of row pairs).
+// (refine and periodic_mean, which choose the passes, are set.)
 template <typename T> int xpass_parts(const XParams<T>& p);
 
 // Pass along a strided axis: pencils p of length L with elements at
@@ -184,6 +185,8 @@ template <typename T> void launch_plane_table(const PlaneShape& sh, const double
 struct LengthPasses {
   int L, L1, L2;            // L = L1 L2
   int P;                    // row pairs per work-group of the x passes
+  bool six64;               // FP64 solves on full rows with six fields (refinement, the mean
+                            // term) take the two-level x passes
   void (*strided32)(int mode, const SParams<float>& p, hipStream_t s);
   void (*strided64)(int mode, const SParams<double>& p, hipStream_t s);
   bool (*xfwd32)(int mode, const XParams<float>& p, hipStream_t s);
@@ -198,6 +201,8 @@ bool add_length_passes(const LengthPasses& e);
 constexpr int kFewRows = 4096, kFewRowsLen = 64, kFewRowsPairs = 4;
 bool add_few_rows_passes(const LengthPasses& e);
 bool fast_length(int L);
+// Whether a PCG solve's x passes are the two-level ones.
+template <typename T> bool fast_solve(const XParams<T>& p);
 template <typename T> int fast_xpass_parts(int L, int nrows);
 // 32-bit values that a thread of the FP32 solve's x inverse beside the plane pass holds
 // at once: row loads, operands of lout points per row, twiddles, partial sums.

@@ -34,6 +34,19 @@ def xinv_values(L, lout, periodic):
     return 8 * kp + (6 if periodic else 5) * out + 2 * -(-L // nt) + 2 * shares
 
 
+def two_level_solve(L, lout, elem, six):
+    """Whether PCG solves on rows of lout points (FFT length L) run the two-level x passes; six: the
+    x inverse reads six fields (refinement, the periodic mean term), not five."""
+    if L not in SPLITS:
+        return False
+    if elem == 4 or not six or lout != L:
+        return True
+    P = row_pairs(L)
+    nt = ib.round64(P * max(SPLITS[L]))
+    rows, points = P * -(-(L // 2 + 1) // nt), -(-2 * P * lout // nt)
+    return 2 * (4 * rows + 6 * points) < 528
+
+
 def plane(shape, bc, elem):
     """(vacuum solves and SC/PSD steps, PCG solves) take the plane pass; elem: 4 FP32, 8 FP64."""
     nz, ny, nx = shape

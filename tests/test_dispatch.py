@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import plane_rule
+from test_plane_memory import needs_host, run_host
 from paper_1509_00680_amd import gps
 from test_fft_lengths import SPLITS
 
@@ -77,3 +78,19 @@ def test_plane_pass_rule(bc):
 def test_solves_that_the_pass_slows_down_keep_the_three_passes(shape, bc):
     """Measured 2 to 15 % slower with the plane pass than with the y, z and y passes."""
     assert _footprint(shape, bc, "mixed")[1] == _footprint(shape, bc, "mixed", compact=True)[1]
+
+
+@needs_host
+def test_x_passes_of_solves_on_full_rows():
+    """Which x passes PCG solves launch, at every length, counted on the host."""
+    r = run_host("x_routes.cpp")
+    assert r.returncode == 0, r.stderr[-2000:]
+    generic = set()
+    for line in r.stdout.splitlines():
+        L, bc, precision, refine, route = line.split()
+        L, six = int(L), bc == "periodic" or refine != "0"
+        fast = plane_rule.two_level_solve(L, L, {"fp64": 8, "mixed": 4}[precision], six)
+        assert route == ("two-level" if fast else "generic"), line
+        if L in SPLITS and not fast:
+            generic.add((L, precision))
+    assert generic == {(L, "fp64") for L in (324, 378, 400, 420, 432)}

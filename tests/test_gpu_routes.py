@@ -41,9 +41,9 @@ def _vacuum(shape, bc, precision, f, expect):
     p.close()
 
 
-def _three_iterations(shape, bc, precision, rho, eps):
+def _three_iterations(shape, bc, precision, rho, eps, **kw):
     ref = pcg.pcg_solve(rho, eps, 0.45, bc, tol=1e-30, maxit=3)
-    p = plan(shape, 0.45, bc, precision, maxit=3)
+    p = plan(shape, 0.45, bc, precision, maxit=3, **kw)
     phi = empty(shape)
     assert p.solve_generalized(dev(rho), dev(eps), phi, 1e-30) == gps.GPS_E_NOT_CONVERGED
     assert p.info()["iterations"] == 3
@@ -120,6 +120,21 @@ def test_short_rows_on_both_sides_of_the_row_count(L):
             print("rows", shape, bc, flush=True)
             _vacuum(shape, bc, "mixed", rho, expect)
             _three_iterations(shape, bc, "mixed", rho, eps)
+
+
+@pytest.mark.parametrize("L", [32, 63, 200, 225, 320, 324, 360, 378, 400, 420, 432, 448])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_tracked_solves_on_full_rows(L, precision):
+    """Three iterations that carry the FP64 source of the iterate (refinement on, its first
+    recomputation past the end), on full rows whose x passes are the two-level ones and (FP64,
+    five long lengths) the generic ones."""
+    require_gpu()
+    shape, bc = (6, 4, L), "surface"
+    fast = plane_rule.two_level_solve(L, L, ELEM[precision], True)
+    assert fast == (precision == "mixed" or L not in (324, 378, 400, 420, 432))
+    rho, eps = _fields(shape, bc, L)
+    print("tracked rows", shape, precision, flush=True)
+    _three_iterations(shape, bc, precision, rho, eps, refine_every=100)
 
 
 # shape, boundary condition, element, PCG solves take it

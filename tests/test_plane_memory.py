@@ -40,17 +40,19 @@ def run_host(source, internal=False):
         shutil.rmtree(d, ignore_errors=True)
 
 
-pytestmark = pytest.mark.skipif(shutil.which("g++") is None or
+needs_host = pytest.mark.skipif(shutil.which("g++") is None or
                                 not os.path.exists(os.path.join(ROCM, "include", "hip")),
                                 reason="needs g++ and the HIP headers")
 
 
+@needs_host
 def test_calls_run_where_they_ran_without_the_plane_pass():
     r = run_host("plane_memory.cpp")
     assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
     assert " 0 failures" in r.stdout
 
 
+@needs_host
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
 def test_modes_beside_the_plane_pass():
     r = run_host("plane_modes.cpp", internal=True)
