@@ -995,10 +995,15 @@ void build_graph(gps_plan* pl, int check_neutral, int chunk, int refine) {
 // the GPU idle for about a third of an iteration at 160^3).  first_n > 0 is
 // the caller's guess of the iterations needed (the nonlinear outer loop
 // passes the previous inner solve's count), else the first batch is two
-// chunks.
+// chunks.  warm: the solve starts from the previous one's iterate and may stop
+// at once, so batches of half a chunk come first.  (An iteration past the stop still
+// loads its operands.  Re-solve of an unchanged problem, two chunks -> half a chunk: FP64 189 x
+// 140 x 144 2.42 -> 1.14 ms, mixed 96^3 0.59 -> 0.33; with a charge new by 1e-3 3.37 -> 2.54
+// and 0.77 -> 0.61; with another charge altogether 4.13 -> 3.65, 0.89 -> 0.80, and mixed 32^3, where
+// a poll counts, 0.406 -> 0.419.)
 template <typename T>
 SolveState run_pcg(gps_plan* pl, int check_neutral, const double* track_rho = nullptr,
-                   int first_n = 0) {
+                   int first_n = 0, bool warm = false) {
   Res<T>& R = pl->res<T>();
   const int chunk = pl->opt.check_every;
   // track_rho (the right-hand side): the x passes keep the FP64 source s of
@@ -1016,7 +1021,8 @@ SolveState run_pcg(gps_plan* pl, int check_neutral, const double* track_rho = nu
   b.n = 1;
   b.slot[0] = 0;
   int k = 0;              // iterations enqueued
-  int n = first_n > 0 ? std::min(first_n, 8 * chunk) : 2 * chunk;   // before the next poll
+  const int unknown = warm ? std::max(1, chunk / 2) : 2 * chunk;   // without a rate
+  int n = first_n > 0 ? std::min(first_n, 8 * chunk) : unknown;    // before the next poll
   double prev_rr = -1.0;
   int prev_it = 0;
   SolveState st{};
@@ -1057,7 +1063,7 @@ SolveState run_pcg(gps_plan* pl, int check_neutral, const double* track_rho = nu
     // risen) is followed by half the iterations done; a solve from scratch
     // waits for a rate between two polls, two chunks apart.
     const bool prior = first_n > 0;
-    n = prior ? std::max(1, std::min(2 * chunk, st.iters / 2)) : 2 * chunk;
+    n = prior ? std::max(1, std::min(2 * chunk, st.iters / 2)) : unknown;
     const bool from_start = prior && prev_rr < 0.0;
     if (from_start) {
       prev_rr = st.rr0;
@@ -1179,7 +1185,7 @@ gps_status solve_impl(gps_plan* pl, const double* rho, const double* eps, double
   if (!nonlinear) {
     // warm start: phi_0 = S^-1 G s and r_0 = b - A phi_0 from the kept source
     if (warm) refine_step<T>(pl, rho, false);
-    const SolveState st = run_pcg<T>(pl, periodic && !el.present, track ? rho : nullptr);
+    const SolveState st = run_pcg<T>(pl, periodic && !el.present, track ? rho : nullptr, 0, warm);
     R.have_src = track && (st.status == GPS_OK || st.status == GPS_E_NOT_CONVERGED);
     finish_info<T>(pl, st, rho, phi, st.iters);
     pl->info.status = st.status;

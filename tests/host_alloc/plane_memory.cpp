@@ -150,6 +150,28 @@ static void timed(int refine) {
   }
 }
 
+// A solve that starts from the previous iterate may need no iteration at all, so few are
+// queued before its first poll (every state that is read here says done): half a chunk, two
+// chunks without an iterate to start from.
+static void warm() {
+  fake::limit = ~size_t(0);
+  const Kind k{"warm", GPS_PREC_FP64, false, 0, nullptr};
+  gps_plan* p = make(GPS_BC_FREE, k, false);
+  gps_options o;
+  gps_plan_get_options(p, &o);
+  o.warm_start = 1;
+  EXPECT(gps_plan_set_options(p, &o) == GPS_OK, "options");
+  EXPECT(gps_plan_set_timing(p, GPS_K_YFWD) == GPS_OK, "timing");
+  for (int call = 0; call < 3; ++call) {
+    fake::launches.clear();
+    EXPECT(gps_solve_generalized(p, rho.data(), eps.data(), phi.data(), 1e-6) == GPS_OK, "warm");
+    const int queued = fake::count("k_fxfwdIdLi8ELi4ELi6ELi3E");   // XF_SOLVE_REF at length 32
+    const int expect = call == 0 ? 2 * o.check_every : o.check_every / 2;
+    EXPECT(queued == expect, "call %d: %d iterations before the first poll", call, queued);
+  }
+  gps_plan_destroy(p);
+}
+
 // A plan is made within the bytes that one without the pass needs at the most, and allocates
 // nothing after it has freed its transient (the next plan then finds both blocks again).
 static void create(int bc) {
@@ -257,6 +279,7 @@ int main() {
       if (periodic && (k.refine > 0 || std::strncmp(k.name, "sc", 2) == 0)) continue;
       run(bc, k);
     }
+  warm();
   timed(0);
   timed(5);
   for (int bc : {GPS_BC_FREE, GPS_BC_SURFACE, GPS_BC_PERIODIC, GPS_BC_WIRE}) {
