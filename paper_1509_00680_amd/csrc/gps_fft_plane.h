@@ -21,11 +21,14 @@
 // reads and its writes, and the z pass keeps the second factor's values in
 // registers from the forward transform over the multiplication to the inverse.
 //
-// Bound by the latency of its seven steps at small planes and by arithmetic (a CU
-// runs one or two work-groups) at the largest; it wins by the launches and the
-// transposes through memory that it saves.  Against the y, z and y passes:
-// generalized Poisson 32^3 FP32 1113 -> 1020 us, 96^3 FP32 3834 -> 3548 us (kernels 29.4
-// -> 22.0 us an iteration, the x inverse + 4), vacuum solve 24^3 FP64 31.5 -> 28.6 us.
+// Bound by the latency of its seven steps, over few work-groups: 50 on 256 CUs at 24^3, 66
+// at 32^3, 194 at 96^3 (of 152 KB LDS, so at most one per CU).  It wins by the launches
+// and the transposes through memory that it saves.  Plans with and without it in turn, one
+// MI355X: mixed solves at 1e-6 of 32^3 1086 -> 973 us, 64^3 1645 -> 1481, 96^3 3820 -> 3580 (kernels
+// 29.4 -> 20.6 us an iteration, the x inverse + 3.5), vacuum solve 24^3 FP64 29.5 -> 26.8 us, SC
+// 60^3 FP64 1921 -> 1861 us.  Errors against FP64, over those of the three passes: FP32 vacuum
+// solves 0.975 to 1.035, mean 1.006 (12 grids, 30 solutes each), mixed solves 0.92 to
+// 1.04, mean 1.008: the fold's extra twiddle product is no more than their scatter.
 #pragma once
 
 #include <cstdint>
