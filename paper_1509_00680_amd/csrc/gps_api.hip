@@ -303,9 +303,9 @@ SParams<T> sparams(const gps_plan* pl, int axis, int L, int Lin, int Lout, int n
 }
 
 // The plane pass's own memory is optional.  Where the device has no room for a call beside
-// it, the plan gives it back (tables and half spectra) and keeps to the y, z, y passes; the
-// half spectra are allocated last, when a call has all that it needs: by every call
-// where PCG solves take the pass, else by the vacuum solve and SC/PSD alone.
+// it, the plan gives it back (tables and half spectra), keeps to the y, z, y passes and
+// tries again.  Where PCG solves take the pass every slot has a half spectrum, else the
+// vacuum solve and SC/PSD allocate slot 0's last, when they have all that they need.
 bool give_back_plane(gps_plan* pl);
 
 template <typename F>
@@ -493,6 +493,8 @@ void alloc_slot(gps_plan* pl, Slot<T>& s, size_t* bytes) {
   if (pl->bc == GPS_BC_PERIODIC) dalloc(&s.s, nb, bytes);
   dalloc(&s.sq64, (size_t)n * sizeof(double), bytes);
   dalloc(&s.work, (size_t)g.nz * g.Ly * g.Kx * sizeof(cplx<T>), bytes);
+  if (pl->shape<T>().N > 0 && pl->shape<T>().solve)   // PCG solves take the plane pass
+    dalloc(&s.half, (size_t)g.nz * g.ny * g.Kx * sizeof(cplx<T>), bytes);
   dalloc(&s.part_init, (size_t)4 * nvg * sizeof(double), bytes);
   dalloc(&s.part_rr, (size_t)nxg * sizeof(double), bytes);
   dalloc(&s.part_delta, (size_t)nzg * sizeof(double), bytes);
@@ -514,7 +516,7 @@ void free_slot(Slot<T>& s) {
 
 template <typename T> void free_res(gps_plan* pl);
 
-// What the solves of one precision need (all but the plane pass's half spectra).
+// What the solves of one precision need.
 template <typename T>
 void grow_res(gps_plan* pl, bool need_ion, bool need_refine) {
   Res<T>& R = pl->res<T>();
@@ -591,25 +593,20 @@ void ensure_half(gps_plan* pl) {
   if (pl->shape<T>().N == 0) return;
   Res<T>& R = pl->res<T>();
   const Geom& g = pl->g;
-  bool changed = false;
+  if (R.slot().half) return;
   try {
-    for (int i = 0; i < R.nslots; ++i) {
-      if (R.slot(i).half) continue;
-      dalloc(&R.slot(i).half, (size_t)g.nz * g.ny * g.Kx * sizeof(cplx<T>), &R.bytes);
-      changed = true;
-    }
+    dalloc(&R.slot().half, (size_t)g.nz * g.ny * g.Kx * sizeof(cplx<T>), &R.bytes);
   } catch (const NoMem&) {
     give_back_plane(pl);
     return;
   }
-  if (changed) drop_graphs(R);           // the slot table changed
+  drop_graphs(R);                        // the slot table changed
 }
 
 template <typename T>
 void ensure_res(gps_plan* pl, bool need_ion, bool need_refine = false) {
   std::lock_guard<std::mutex> lk(g_plan_mu);
   with_room(pl, [&] { grow_res<T>(pl, need_ion, need_refine); });
-  if (pl->shape<T>().solve) ensure_half<T>(pl);
 }
 
 template <typename T>
@@ -1457,7 +1454,6 @@ void ensure_batch(gps_plan* pl, int K) {
         ++R.nslots;
       }
     });
-    if (pl->shape<T>().solve) ensure_half<T>(pl);
   }
   if (!R.h_states) halloc(&R.h_states, kArgSlots * sizeof(SolveState));
 }

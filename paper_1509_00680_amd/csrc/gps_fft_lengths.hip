@@ -35,9 +35,16 @@ constexpr int even_pairs(int m) {
   return best;
 }
 
+template <int A, int B, int P> static bool add_length() {
+  bool ok = add_length_passes(TwoLevel<A, B, P, false>::passes());
+  if constexpr (A * B <= kFewRowsLen)
+    ok = add_few_rows_passes(TwoLevel<A, B, kFewRowsPairs, false>::x_passes32()) && ok;
+  return ok;
+}
+
 #define GPS_LENGTH(A, B)           \
   static const bool len_##A##_##B = \
-      add_length<A, B, even_pairs(larger(A, B)), false>();
+      add_length<A, B, even_pairs(larger(A, B))>();
 
 #if GPS_LENGTH_GROUP == 0
 GPS_LENGTH(4, 5)

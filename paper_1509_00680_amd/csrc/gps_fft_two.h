@@ -1040,12 +1040,4 @@ template <int L1, int L2, int P, bool TUNED> struct TwoLevel {
   }
 };
 
-// Adds the entries of a length.
-template <int L1, int L2, int P, bool TUNED> bool add_length() {
-  bool ok = add_length_passes(TwoLevel<L1, L2, P, TUNED>::passes());
-  if constexpr (L1 * L2 <= kFewRowsLen)
-    ok = add_few_rows_passes(TwoLevel<L1, L2, kFewRowsPairs, TUNED>::x_passes32()) && ok;
-  return ok;
-}
-
 }  // namespace gps

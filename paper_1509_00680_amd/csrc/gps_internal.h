@@ -157,8 +157,8 @@ struct PlaneShape {
   int A1, A2, C1, C2;
   int PY;                     // LDS pitch of a row of N elements
   int threads;
-  int padz;
-  int solve;                  // PCG solves take the pass (else vacuum solves and SC/PSD alone)
+  short padz;
+  short solve;                // PCG solves take the pass (else vacuum solves and SC/PSD alone)
   size_t lds;                 // bytes
   FastDiv div_A2, div_nz, div_N, div_ny;
 };
