@@ -24,9 +24,9 @@
 // Bound by the latency of its seven steps, over few work-groups: 50 on 256 CUs at 24^3, 66
 // at 32^3, 194 at 96^3 (of 152 KB LDS, so at most one per CU).  It wins by the launches
 // and the transposes through memory that it saves.  Plans with and without it in turn, one
-// MI355X: mixed solves at 1e-6 of 32^3 1086 -> 973 us, 64^3 1645 -> 1481, 96^3 3820 -> 3580 (kernels
-// 29.4 -> 20.6 us an iteration, the x inverse + 3.5), vacuum solve 24^3 FP64 29.5 -> 26.8 us, SC
-// 60^3 FP64 1921 -> 1861 us.  Errors against FP64, over those of the three passes: FP32 vacuum
+// MI355X: mixed solves at 1e-6 of 32^3 1095 -> 976 us, 64^3 1655 -> 1486, 96^3 3848 -> 3555 (kernels
+// 29.4 -> 20.0 us an iteration, the x inverse + 3.5), vacuum solve 24^3 FP64 29.7 -> 26.4 us, SC
+// 60^3 FP64 1953 -> 1892 us.  Errors against FP64, over those of the three passes: FP32 vacuum
 // solves 0.975 to 1.035, mean 1.006 (12 grids, 30 solutes each), mixed solves 0.92 to
 // 1.04, mean 1.008: the fold's extra twiddle product is no more than their scatter.
 #pragma once
